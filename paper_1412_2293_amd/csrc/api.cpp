@@ -999,7 +999,10 @@ static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char
             const int64_t init = p == 0 ? (int64_t)init_index : -1;
             uint64_t *otab = (uint64_t *)(B + L.wtab);
             char *wtab = B + L.wtab + align256((size_t(1) << (n > P.K ? n - P.K : 0)) * sizeof(uint64_t));
-            QS_HIP(launch_pass_prep(dt, S, &P.passes[p], pdv, tab, gdev, B + L.rec, (int64_t)init_index, dyn, st));
+            if (P.passes[p].expand)
+                QS_HIP(launch_expand_prep(dt, S, &P.passes[p], (int)p, pdv, tab, B + L.rec, (int64_t)init_index, dyn, st));
+            else
+                QS_HIP(launch_pass_prep(dt, S, &P.passes[p], pdv, tab, gdev, B + L.rec, (int64_t)init_index, dyn, st));
             bool blocks = false;
             for (int ri = P.passes[p].round_begin; ri < P.passes[p].round_end; ++ri)
                 blocks = blocks || P.rounds[ri].block_rec >= 0;
@@ -1025,13 +1028,16 @@ static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char
                 return QS_OK;
             }
             // otherwise the last pass also forms the overlaps with slot 0: slot 0 first, then the
-            // others
-            QS_HIP(launch_fused_pass(psi, dt, n, S, &P.passes[p], (int)p, init, (int64_t)init_index, pdv, B + L.rec,
-                                     wtab, otab, st, dyn, part, 0, 1));
-            if (S > 1)
-                QS_HIP(launch_fused_pass(psi, dt, n, S, &P.passes[p], (int)p, init, (int64_t)init_index, pdv,
-                                         B + L.rec, wtab, otab, st, dyn, part, 1, S - 1));
-            QS_HIP(launch_overlap_final(psi, dt, n, S, fused_walked_bits(n, &P.passes[p], init), pmarked, part,
+            // others, which read its amplitudes (an expanding pass: the others first, which form
+            // its amplitudes from its inputs)
+            const bool ref_last = P.passes[p].expand != 0;
+            for (int k = 0; k < 2; ++k) {
+                const bool others = (k == 0) == ref_last;
+                if (others && S == 1) continue;
+                QS_HIP(launch_fused_pass(psi, dt, n, S, &P.passes[p], (int)p, init, (int64_t)init_index, pdv, B + L.rec,
+                                         wtab, otab, st, dyn, part, others ? 1 : 0, others ? S - 1 : 1));
+            }
+            QS_HIP(launch_overlap_final(psi, dt, n, S, fused_partial_bits(n, &P.passes[p], init), pmarked, part,
                                         (double *)(B + L.out), st, dyn));
             return QS_OK;
         }
@@ -1215,6 +1221,7 @@ qs_status qs_plan_describe(const qs_gate *gates, int n_gates, int n, qs_dtype dt
         I("uni_kernel", pd.uni_kernel);
         I("zin_ops", pd.zin_ops);
         I("mixed_ops", pd.mixed_ops);
+        I("expand", pd.expand);
         I("rec_size", pd.rec_size);
         I("load_round", pd.load_round);
         I("load_reg_mask", P.rounds[pd.load_round].reg_mask);

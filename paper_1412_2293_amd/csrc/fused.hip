@@ -11,53 +11,14 @@
 // qubit, which is a tile-constant, thread-constant or register bit here.
 #include <type_traits>
 
+#include "cplx.h"
 #include "internal.h"
 
 namespace qs {
 
-template <typename R>
-struct cxf {
-    R re, im;
-};
-
-template <typename R>
-__device__ __forceinline__ cxf<R> mul(cxf<R> a, cxf<R> b)
-{
-    return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
-}
-
-template <typename R>
-__device__ __forceinline__ cxf<R> fma_c(cxf<R> a, cxf<R> b, cxf<R> c)
-{
-    return {a.re * b.re - a.im * b.im + c.re, a.re * b.im + a.im * b.re + c.im};
-}
-
-// Register-tile element: one complex amplitude as a two-lane vector, so that the compiler keeps
-// it in an aligned register pair and moves it with one 64-bit move.
-template <typename R>
-using tv = R __attribute__((ext_vector_type(2)));
-template <typename R>
-__device__ __forceinline__ cxf<R> cx(tv<R> v) { return {v.x, v.y}; }
-template <typename R>
-__device__ __forceinline__ tv<R> tvec(cxf<R> c) { return tv<R>{c.re, c.im}; }
-
 __device__ __forceinline__ uint32_t swz(uint32_t l)
 {
     return lds_swizzle(l);
-}
-
-// Deposit the low bits of x into the set bits of mask (lowest first).
-__device__ __forceinline__ uint32_t deposit32(uint32_t x, uint32_t mask, int K)
-{
-    uint32_t out = 0;
-    int b = 0;
-    for (int j = 0; j < K; ++j) {
-        if (mask & (1u << j)) {
-            out |= ((x >> b) & 1u) << j;
-            ++b;
-        }
-    }
-    return out;
 }
 
 template <int RB>
@@ -432,11 +393,6 @@ __device__ __forceinline__ void dispatch_phase_on_bit(int p, tv<R> (&a)[1 << RB]
 // ---------------------------------------------------------------------------------------
 // Per-slot records of one pass (one thread per op and slot; FP64 products rounded once).
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ double2 dmul(double2 a, double2 b)
-{
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
 __device__ __forceinline__ double2 dconj(double2 a) { return make_double2(a.x, -a.y); }
 
 // a / |a| (1 for a == 0)
@@ -1429,6 +1385,9 @@ hipError_t launch_fused_pass(void *psi, qs_dtype dt, int n, int S, const PassDes
                              double *ovl, int slot_base, int slots)
 {
     const PassDesc &h = *pass_host;
+    if (h.expand)
+        return launch_expand_pass(psi, dt, n, S, pass_host, pass_index, init, basis, prog, rec, wtab, otab, st, dyn, ovl,
+                                  slot_base, slots);
     size_t lds = fused_lds_bytes(dt, h.K);
     const int rec_cap = stage_rec_cap(dt, h.K);
     if (lds > 160 * 1024 || rec_cap <= 0 || basis < 0) return hipErrorInvalidValue;

@@ -109,7 +109,15 @@ struct PassDesc {
                                   // a uniform output factor; 4 none, each with a real matrix and
                                   // no folded phase; 5 the pass has no one-qubit op
     int32_t mixed_ops;            // the pass has ops other than one-qubit gates
+    int32_t expand;               // zin_ops 3 with enough targets: the pass is the product of its
+                                  // targets' factors (see k_expand) and runs as one
+    int16_t xop[16];              // expand: op (relative to op_begin) of tile-local bit j, -1 none
 };
+
+// Expanding passes: register bits are the kExpandRegs highest targets of the tile (complex<float>
+// takes one fewer, and the two amplitudes of a 16-byte vector).
+constexpr int kExpandRegs = 4;
+constexpr int kExpandSlots = 4;   // most slots one workgroup expands
 
 // A stage: consecutive rounds whose records, outer jobs and outer bits stay within the
 // per-stage bounds below (record and job offsets of ops are relative to the pass; stage ranges
@@ -296,8 +304,19 @@ hipError_t launch_fused_pass(void *psi, qs_dtype dt, int n, int S, const PassDes
 // also writes each (slot, tile) block's FP64 sums Re/Im <psi_0|psi_slot> and <psi_slot|psi_slot>
 // to ovl[((slot << walked bits) | tile) * 3 ...]; slot 0's tiles must be final before a launch
 // with slot_base > 0 (run slot 0 alone first).  Finished by launch_overlap_final.
+// The records of a pass marked `expand` (instead of launch_pass_prep).
+hipError_t launch_expand_prep(qs_dtype dt, int S, const PassDesc *pass_host, int pass_index, ProgramDev prog,
+                              const double *tab, void *rec, int64_t basis, const RunParams *dyn, hipStream_t st);
+// A pass marked `expand`: the arguments and results of launch_fused_pass, except that a launch
+// with slot_base > 0 comes before slot 0's (it forms slot 0's amplitudes from its inputs).
+hipError_t launch_expand_pass(void *psi, qs_dtype dt, int n, int S, const PassDesc *pass_host, int pass_index,
+                              int64_t init, int64_t basis, ProgramDev prog, const void *rec, const void *wtab,
+                              const uint64_t *otab, hipStream_t st, const RunParams *dyn, double *ovl, int slot_base,
+                              int slots);
 // Walked tile-number bits of a pass launch (the tiles its blocks cover).
 int fused_walked_bits(int n, const PassDesc *pass_host, int64_t init);
+// Overlap partials per slot of a pass launched with ovl: 2^(these bits).
+int fused_partial_bits(int n, const PassDesc *pass_host, int64_t init);
 // The operand tables of the pass's block rounds (after launch_pass_prep of the pass; complex<float>
 // plans only).
 hipError_t launch_block_prep(qs_dtype dt, int S, const PassDesc *pass_host, ProgramDev prog, void *rec,

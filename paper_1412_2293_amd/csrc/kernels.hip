@@ -698,36 +698,49 @@ __global__ void __launch_bounds__(kRedThreads) k_overlap_partial(const R *ref, c
     }
 }
 
+// One workgroup per slot.  Each thread keeps four partials in flight (a slot of 2^26 amplitudes
+// has 2^14 of them: with one at a time the sum waited 64 load latencies, 32 us), and the sums meet
+// over the lanes of each wave, then over the waves, in a fixed order.
+constexpr int kFinalThreads = 1024;
+
 template <typename R>
-__global__ void __launch_bounds__(kRedThreads) k_overlap_final(const R *psi, int n, int log_blocks,
-                                                               int64_t marked, const double *partials,
-                                                               double *out, const RunParams *dyn)
+__global__ void __launch_bounds__(kFinalThreads) k_overlap_final(const R *psi, int n, int log_blocks, int64_t marked,
+                                                                 const double *partials, double *out,
+                                                                 const RunParams *dyn)
 {
-    __shared__ double sh[3 * kRedThreads];
+    __shared__ double sh[3][kFinalThreads / 64];
     if (dyn) marked = dyn->marked;
-    const int slot = blockIdx.x;
+    const int slot = blockIdx.x, t = (int)threadIdx.x;
     const int nb = 1 << log_blocks;
-    double v[4] = {0, 0, 0, 0};
-    for (int b = threadIdx.x; b < nb; b += kRedThreads) {
-        const double *q = partials + ((uint64_t)slot * nb + b) * 3;
-        v[0] += q[0];
-        v[1] += q[1];
-        v[2] += q[2];
+    const double *q = partials + (uint64_t)slot * nb * 3;
+    double v[3] = {0, 0, 0};
+    for (int b = t; b < nb; b += 4 * kFinalThreads) {
+        double x[4][3];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const int i = b + u * kFinalThreads;
+                x[u][k] = i < nb ? q[(uint64_t)i * 3 + k] : 0.0;
+            }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) v[k] += x[u][k];
     }
-    block_sum(sh, v, 3);
-    if (threadIdx.x == 0) {
-        double *o = out + (uint64_t)slot * 5;
-        o[0] = v[0];
-        o[1] = v[1];
-        o[2] = v[2];
-        if (marked >= 0) {
-            const R *p = psi + ((uint64_t)slot << (n + 1));
-            o[3] = (double)p[2 * marked];
-            o[4] = (double)p[2 * marked + 1];
-        } else {
-            o[3] = 0.0;
-            o[4] = 0.0;
-        }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
+        if ((t & 63) == 0) sh[k][t >> 6] = v[k];
+    }
+    __syncthreads();
+    double *o = out + (uint64_t)slot * 5;
+    if (t < 3) {
+        double a = 0.0;
+        for (int w = 0; w < kFinalThreads / 64; ++w) a += sh[t][w];
+        o[t] = a;
+    } else if (t < 5) {
+        o[t] = marked >= 0 ? (double)psi[((uint64_t)slot << (n + 1)) + 2 * marked + (t - 3)] : 0.0;
     }
 }
 
@@ -1067,10 +1080,10 @@ hipError_t launch_overlap_final(const void *psi, qs_dtype dt, int n, int S, int 
 {
     TimedLaunch tl("reduce", (double)((uint64_t)S << log_blocks) * 3 * sizeof(double), st);
     if (dt == QS_C64)
-        hipLaunchKernelGGL(k_overlap_final<float>, dim3(S), dim3(kRedThreads), 0, st, (const float *)psi, n,
+        hipLaunchKernelGGL(k_overlap_final<float>, dim3(S), dim3(kFinalThreads), 0, st, (const float *)psi, n,
                            log_blocks, marked, partials, out, dyn);
     else
-        hipLaunchKernelGGL(k_overlap_final<double>, dim3(S), dim3(kRedThreads), 0, st, (const double *)psi, n,
+        hipLaunchKernelGGL(k_overlap_final<double>, dim3(S), dim3(kFinalThreads), 0, st, (const double *)psi, n,
                            log_blocks, marked, partials, out, dyn);
     return hipGetLastError();
 }
@@ -1087,13 +1100,13 @@ hipError_t launch_overlaps(const void *ref_psi, int ref_slot, const void *psi, q
         const float *ref = (const float *)ref_psi + ((uint64_t)ref_slot << (n + 1));
         hipLaunchKernelGGL(k_overlap_partial<float>, dim3(nblk), dim3(kRedThreads), 0, st, ref,
                            (const float *)psi, n, lb, partials);
-        hipLaunchKernelGGL(k_overlap_final<float>, dim3(S), dim3(kRedThreads), 0, st,
+        hipLaunchKernelGGL(k_overlap_final<float>, dim3(S), dim3(kFinalThreads), 0, st,
                            (const float *)psi, n, lb, marked, partials, out, dyn);
     } else {
         const double *ref = (const double *)ref_psi + ((uint64_t)ref_slot << (n + 1));
         hipLaunchKernelGGL(k_overlap_partial<double>, dim3(nblk), dim3(kRedThreads), 0, st, ref,
                            (const double *)psi, n, lb, partials);
-        hipLaunchKernelGGL(k_overlap_final<double>, dim3(S), dim3(kRedThreads), 0, st,
+        hipLaunchKernelGGL(k_overlap_final<double>, dim3(S), dim3(kFinalThreads), 0, st,
                            (const double *)psi, n, lb, marked, partials, out, dyn);
     }
     return hipGetLastError();

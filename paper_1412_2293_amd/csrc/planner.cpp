@@ -422,6 +422,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
 
     // 4. tiles, rounds and per-slot records
     int max_rec = 0;
+    std::vector<int> pg_target;   // per op: its (first) physical qubit
     uint64_t touched = 0;   // physical qubits targeted by non-diagonal gates of earlier passes
     for (size_t pi = 0; pi < passes.size(); ++pi) {
         PassBuild &pb = passes[pi];
@@ -726,6 +727,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                 }
                 op.pref_end = (int)P.prefs.size();
                 P.ops.push_back(op);
+                pg_target.push_back(x.a);
             }
             R.op_end = (int)P.ops.size();
             // A round of one-qubit ops (at least three) on the four register bits runs as one dense
@@ -859,6 +861,21 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                 }
             }
         }
+        // A pass of kind 3 has one op per target, each multiplying by a factor of its own bit, so
+        // its result is the product of the targets' factors times the untouched amplitudes: it runs
+        // as an expansion when four targets lie above the four lowest tile-local bits (registers;
+        // the lanes keep rows of at least 16 amplitudes) and the tile gives whole waves of threads.
+        for (int j = 0; j < 16; ++j) pd.xop[j] = -1;
+        if (pd.zin_ops == 3 && K >= 10 && K <= 12 && Q[0] == 0) {
+            int high = 0;
+            for (int oi = pd.op_begin; oi < (int)P.ops.size(); ++oi) {
+                const int j = local_of[pg_target[oi]];
+                pd.xop[j] = (int16_t)(oi - pd.op_begin);
+                high += j >= 4;
+            }
+            pd.expand = high >= kExpandRegs;
+            if (pd.expand) rec = std::max(rec, 2 * K);   // its records start with 2 K factors
+        }
         pd.op_end = (int)P.ops.size();
         pd.job_end = (int)P.jobs.size();
         pd.rec_size = rec;
@@ -869,7 +886,10 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
     // The first pass stores the zero tiles unless the last pass rewrites every amplitude (no
     // tile-number bit of it is still classical); every other pass reads only amplitudes of the
     // support, which the pass before it wrote.
-    if (!P.passes.empty()) P.passes.front().zero_fill = P.passes.back().classical != 0;
+    if (!P.passes.empty()) {
+        P.passes.front().zero_fill = P.passes.back().classical != 0;
+        if (P.passes.front().zero_fill) P.passes.front().expand = 0;   // stores zero tiles too
+    }
     P.max_rec = max_rec;
     return QS_OK;
 }
