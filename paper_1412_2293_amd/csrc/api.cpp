@@ -557,7 +557,7 @@ qs_status qs_timing_reset(void)
 namespace {
 
 struct TrajLayout {
-    size_t states, tab, gates, edev, passes, stages, rounds, ops, prefs, jobs, obits, chains, wtab, rec, partials, out,
+    size_t states, tab, gates, edev, passes, stages, rounds, ops, prefs, jobs, obits, sops, chains, wtab, rec, partials, out,
         dyn, total;
 };
 
@@ -580,8 +580,9 @@ qs_status fused_plan_for(const qs_gate *gates, int n_gates, int n, qs_dtype dt, 
         K = n;   // the whole state is one tile: the circuit runs as one launch
         if (RB > K) RB = K;
     }
+    const bool state = K == n && !mfma && state_shape(dt, n, RB);
     // wide register tiles (16 complex<float>, 8 or 16 complex<double>) run 256-thread blocks
-    if ((RB == 4 || (dt == QS_C128 && RB == 3)) && K - RB > 8)
+    if (!state && (RB == 4 || (dt == QS_C128 && RB == 3)) && K - RB > 8)
         return fail(QS_EINVAL, "plan: this register tile allows at most 256 threads (tile_bits - reg_bits <= 8)");
     out.K = K;
     out.RB = RB;
@@ -589,7 +590,7 @@ qs_status fused_plan_for(const qs_gate *gates, int n_gates, int n, qs_dtype dt, 
     int rec_cap = stage_rec_cap(dt, K);
     if (rec_cap < 256) return fail(QS_EINVAL, "plan: tile leaves too little LDS for the gate records");
     out.mfma = mfma && dt == QS_C64 && RB == 4;
-    return plan_fused(gates, n_gates, n, K, RB, run, rec_cap, out.prog, out.mfma);
+    return plan_fused(gates, n_gates, n, K, RB, run, rec_cap, out.prog, out.mfma, state);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -705,6 +706,21 @@ qs_status autotune_plan(const qs_gate *gates, int n_gates, int n, qs_dtype dt, i
     double best = model_cost_unfused(gates, n_gates, n, dt, S);
     out = Plan();
     out.fused = false;
+    // a state that one workgroup holds runs its whole circuit there: no state traffic between
+    // passes and one launch, whatever the other shapes cost
+    if (const int rb = state_reg_bits(dt, n)) {
+        Plan cand;
+        if (fused_plan_for(gates, n_gates, n, dt, n, rb, 4, cand) == QS_OK) {
+            const double cost = model_cost_fused(cand.prog, n, dt, S, cand.run_bits);
+            if (cost < best * 0.999) {
+                out = std::move(cand);
+                if (cost_out) *cost_out = cost;
+                return QS_OK;
+            }
+        } else {
+            clear_error();
+        }
+    }
     const int ncand = dt == QS_C64 ? (int)(sizeof kCandC64 / sizeof kCandC64[0])
                                    : (int)(sizeof kCandC128 / sizeof kCandC128[0]);
     for (int c = 0; c < ncand; ++c) {
@@ -772,6 +788,7 @@ TrajLayout traj_layout(int n, qs_dtype dt, int T, int n_gates, const Plan &pl)
     L.prefs = take(std::max<size_t>(pl.prog.prefs.size(), 1) * sizeof(PrepRef));
     L.jobs = take(std::max<size_t>(pl.prog.jobs.size(), 1) * sizeof(OuterJob));
     L.obits = take(std::max<size_t>(pl.prog.obits.size(), 1) * sizeof(int32_t));
+    L.sops = take(std::max<size_t>(pl.prog.sops.size(), 1) * sizeof(StateOp));
     L.chains = take(std::max<size_t>(pl.prog.chain_gates.size() + pl.prog.chain_off.size(), 1) * sizeof(int32_t));
     // the tiles' outer index bits (at most 2^(n - K) tiles), then the per (slot, tile, outer job)
     // phase products of the pass being run
@@ -909,6 +926,7 @@ static TrajLayout prep_layout(const TrajPrep &prep, int T)
     pl.prog.prefs.resize(prep.prog.prefs.size());
     pl.prog.jobs.resize(prep.prog.jobs.size());
     pl.prog.obits.resize(prep.prog.obits.size());
+    pl.prog.sops.resize(prep.prog.sops.size());
     pl.prog.chain_gates.resize(prep.prog.chain_gates.size());
     pl.prog.chain_off.resize(prep.prog.chain_off.size());
     pl.prog.max_rec = prep.prog.max_rec;
@@ -946,6 +964,7 @@ static void build_prog_image(TrajPrep &prep)
     put(L.prefs, P.prefs.data(), sizeof(PrepRef) * P.prefs.size());
     put(L.jobs, P.jobs.data(), sizeof(OuterJob) * P.jobs.size());
     put(L.obits, P.obits.data(), sizeof(int32_t) * P.obits.size());
+    put(L.sops, P.sops.data(), sizeof(StateOp) * P.sops.size());
     put(L.chains, P.chain_off.data(), sizeof(int32_t) * P.chain_off.size());
     put(L.chains + sizeof(int32_t) * P.chain_off.size(), P.chain_gates.data(), sizeof(int32_t) * P.chain_gates.size());
 }
@@ -965,8 +984,10 @@ static qs_status upload_program(const TrajPrep &prep, const TrajLayout &L, char 
 // Noise table, initial state, the circuit (fused passes or per-gate sweeps) and the FP64
 // reductions into L.out.  With dyn non-null the seed, request, trajectory base, initial index
 // and marked index come from device memory (captured graphs).
+// overlaps false: the caller needs none (a density matrix).
 static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char *B, int S, uint64_t init_index,
-                                 int64_t pmarked, const qs_noise *nz, const RunParams *dyn, hipStream_t st)
+                                 int64_t pmarked, const qs_noise *nz, const RunParams *dyn, hipStream_t st,
+                                 bool overlaps = true)
 {
     const int n = prep.n;
     const qs_dtype dt = prep.dt;
@@ -994,7 +1015,7 @@ static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char
         ProgramDev pdv{(const PassDesc *)(B + L.passes), (const StageDesc *)(B + L.stages),
                        (const RoundDesc *)(B + L.rounds), (const OpDesc *)(B + L.ops),
                        (const PrepRef *)(B + L.prefs), (const OuterJob *)(B + L.jobs),
-                       (const int32_t *)(B + L.obits)};
+                       (const int32_t *)(B + L.obits), (const StateOp *)(B + L.sops)};
         for (size_t p = 0; p < P.passes.size(); ++p) {
             const int64_t init = p == 0 ? (int64_t)init_index : -1;
             uint64_t *otab = (uint64_t *)(B + L.wtab);
@@ -1003,13 +1024,22 @@ static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char
                 QS_HIP(launch_expand_prep(dt, S, &P.passes[p], (int)p, pdv, tab, B + L.rec, (int64_t)init_index, dyn, st));
             else
                 QS_HIP(launch_pass_prep(dt, S, &P.passes[p], pdv, tab, gdev, B + L.rec, (int64_t)init_index, dyn, st));
+            if (P.passes[p].state) {
+                // one workgroup per slot holds the state: every slot in one launch, the overlaps
+                // from the stored states
+                QS_HIP(launch_state_pass(psi, dt, n, S, &P.passes[p], (int)p, init, pdv, B + L.rec, st, dyn));
+                if (overlaps)
+                    QS_HIP(launch_overlaps(psi, 0, psi, dt, n, S, pmarked, (double *)(B + L.partials),
+                                           (double *)(B + L.out), st, dyn));
+                return QS_OK;
+            }
             bool blocks = false;
             for (int ri = P.passes[p].round_begin; ri < P.passes[p].round_end; ++ri)
                 blocks = blocks || P.rounds[ri].block_rec >= 0;
             if (blocks) QS_HIP(launch_block_prep(dt, S, &P.passes[p], pdv, B + L.rec, st));
             QS_HIP(launch_pass_jobs(dt, n, S, &P.passes[p], pdv, B + L.rec, init, (int64_t)init_index, dyn,
                                     wtab, otab, st));
-            if (p + 1 < P.passes.size()) {
+            if (p + 1 < P.passes.size() || !overlaps) {
                 QS_HIP(launch_fused_pass(psi, dt, n, S, &P.passes[p], (int)p, init, (int64_t)init_index, pdv,
                                          B + L.rec, wtab, otab, st, dyn));
                 continue;
@@ -1056,8 +1086,9 @@ static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char
             }
         }
     }
-    QS_HIP(launch_overlaps(psi, 0, psi, dt, n, S, pmarked, (double *)(B + L.partials), (double *)(B + L.out), st,
-                           dyn));
+    if (overlaps)
+        QS_HIP(launch_overlaps(psi, 0, psi, dt, n, S, pmarked, (double *)(B + L.partials), (double *)(B + L.out), st,
+                               dyn));
     return QS_OK;
 }
 
@@ -1222,6 +1253,7 @@ qs_status qs_plan_describe(const qs_gate *gates, int n_gates, int n, qs_dtype dt
         I("zin_ops", pd.zin_ops);
         I("mixed_ops", pd.mixed_ops);
         I("expand", pd.expand);
+        I("state", pd.state);
         I("rec_size", pd.rec_size);
         I("load_round", pd.load_round);
         I("load_reg_mask", P.rounds[pd.load_round].reg_mask);
@@ -1521,7 +1553,7 @@ qs_status qs_dm_run(const qs_gate *gates, int n_gates, int n_qubits, uint64_t in
     const double zero = 0.0;
     QS_HIP(hipMemcpyAsync(B + D.L.edev, &zero, sizeof zero, hipMemcpyHostToDevice, st));
     const uint64_t init = (init_index << n) | init_index;
-    if ((v = qs::enqueue_compute(prep, D.L, B, 1, init, -1, nullptr, nullptr, st)) != QS_OK) return v;
+    if ((v = qs::enqueue_compute(prep, D.L, B, 1, init, -1, nullptr, nullptr, st, false)) != QS_OK) return v;
     const void *psi_phys = psi_dev;
     if (!identity) {
         QS_HIP(qs::launch_permute_bits(B + D.psi, psi_dev, dt, n, sigma.data(), st));
@@ -1634,7 +1666,8 @@ qs_status qs_traj_graph_create(const qs_gate *gates, int n_gates, int n, qs_dtyp
         return v;
     }
     if ((e = hipStreamSynchronize(g->st)) != hipSuccess) return bail(e, "upload");
-    if ((e = fused_prepare_attributes()) != hipSuccess) return bail(e, "fused kernel attributes");
+    if ((e = fused_prepare_attributes()) != hipSuccess || (e = state_prepare_attributes()) != hipSuccess)
+        return bail(e, "fused kernel attributes");
     const RunParams *dyn = (const RunParams *)(g->buf + g->L.dyn);
     if ((e = hipStreamBeginCapture(g->st, hipStreamCaptureModeThreadLocal)) != hipSuccess)
         return bail(e, "hipStreamBeginCapture");

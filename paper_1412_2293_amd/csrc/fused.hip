@@ -13,6 +13,7 @@
 
 #include "cplx.h"
 #include "internal.h"
+#include "regops.h"
 
 namespace qs {
 
@@ -36,270 +37,6 @@ __device__ __forceinline__ void reg_offsets(uint32_t reg_mask, int K, uint32_t (
             if (r & (1 << k)) o |= pos[k];
         roff[r] = o;
     }
-}
-
-// Phase factors of one folded block for this thread: w (tile and thread constant) and one
-// factor per register bit, applied to a pair when that bit of the pair index is 1.
-template <typename R, int RB>
-struct PhaseSet {
-    cxf<R> w;
-    cxf<R> bit[RB];
-    bool any;
-};
-
-// grec: the block in global memory (uniform reads, held in scalar registers); lrec: the same
-// block staged in LDS (per-thread table lookups); wout: this tile's products of the phases
-// conditioned on tile-number bits (global memory, uniform reads).
-// bits: whether the block has phases conditioned on register bits (else only w is used).
-// uni: no factor of the block depends on a thread-id bit, so every entry of the thread tables
-// equals their first (uniform reads instead of per-thread lookups).
-template <typename R, int RB>
-__device__ __forceinline__ void load_phases(PhaseSet<R, RB> &ps, const cxf<R> *__restrict__ grec,
-                                            const cxf<R> *lrec, bool present, bool bits, bool uni, int job,
-                                            const cxf<R> *wout, uint32_t tid)
-{
-    ps.any = present;
-    if (!present) return;
-    if (bits) {
-#pragma unroll
-        for (int k = 0; k < RB; ++k) ps.bit[k] = grec[k];
-    }
-    if (uni) ps.w = grec[4];
-    else ps.w = mul(lrec[4 + (tid & 31u)], lrec[36 + ((tid >> 5) & 15u)]);
-    if (job >= 0) ps.w = mul(ps.w, wout[job]);
-}
-
-// Phase of the pair at register index r: w, times the register-bit factors when BITS.
-template <typename R, int RB, int P, bool BITS>
-__device__ __forceinline__ cxf<R> pair_phase(const PhaseSet<R, RB> &ps, int r)
-{
-    cxf<R> w = ps.w;
-    if constexpr (BITS) {
-#pragma unroll
-        for (int q = 0; q < RB; ++q)
-            if (q != P && ((r >> q) & 1)) w = mul(w, ps.bit[q]);
-    }
-    return w;
-}
-
-// Register index of the k-th pair (bit P clear) and of the k-th quadruple (bits P0, P1 clear):
-// compile-time integer arithmetic, so that after unrolling every register access is static.
-template <int P>
-__device__ constexpr int pair_base(int k)
-{
-    return ((k >> P) << (P + 1)) | (k & ((1 << P) - 1));
-}
-
-template <int P0, int P1>
-__device__ constexpr int quad_base(int k)
-{
-    constexpr int lo = P0 < P1 ? P0 : P1, hi = P0 < P1 ? P1 : P0;
-    return pair_base<hi>(pair_base<lo>(k));
-}
-
-// PRE: input phase kind (0 none, 1 one factor per thread, 2 with register-bit factors); POST:
-// the folded output block (0 none, 1 one factor per thread, 2 with register-bit factors; with
-// one factor it joins the |1> row of the matrix once per op instead of a product per pair).  ZIN: which input of every pair is known to be
-// zero (0 neither; 1 the |1> input, 2 the |0> input) -- the target qubit has not been touched by
-// any earlier gate of the run and still holds the basis bit 0 (1), so that half of the tile is
-// exactly zero and its products are left out (the result is the same: a product with zero
-// added to a value leaves the value).  They are uniform per op, so each combination is its own
-// straight-line code behind a scalar branch, with no work for an absent block.
-template <typename R, int RB, int P, int PRE, int POST, int ZIN>
-__device__ __forceinline__ void apply_u1(tv<R> (&a)[1 << RB], const cxf<R> (&m0)[4],
-                                         const PhaseSet<R, RB> &pre, const PhaseSet<R, RB> &post)
-{
-    cxf<R> m[4] = {m0[0], m0[1], m0[2], m0[3]};
-    if constexpr (POST == 1) {
-        m[2] = mul(post.w, m[2]);
-        m[3] = mul(post.w, m[3]);
-    }
-#pragma unroll
-    for (int k = 0; k < (1 << (RB - 1)); ++k) {
-        const int r = pair_base<P>(k);
-        const int r1 = r | (1 << P);
-        cxf<R> x0 = cx<R>(a[r]), x1 = cx<R>(a[r1]);
-        cxf<R> y0, y1;
-        if constexpr (ZIN == 1) {
-            y0 = mul(m[0], x0);
-            y1 = mul(m[2], x0);
-        } else {
-            if constexpr (PRE > 0) x1 = mul(pair_phase<R, RB, P, PRE == 2>(pre, r), x1);
-            if constexpr (ZIN == 2) {
-                y0 = mul(m[1], x1);
-                y1 = mul(m[3], x1);
-            } else {
-                y0 = fma_c(m[1], x1, mul(m[0], x0));
-                y1 = fma_c(m[3], x1, mul(m[2], x0));
-            }
-        }
-        if constexpr (POST == 2) y1 = mul(pair_phase<R, RB, P, true>(post, r), y1);
-        a[r] = tvec(y0);
-        a[r1] = tvec(y1);
-    }
-}
-
-// The same update with a real matrix (m[k].im == 0): half the multiplications.  A one-factor
-// output block makes the |1> row complex (m2 w, m3 w).
-template <typename R, int RB, int P, int PRE, int POST, int ZIN>
-__device__ __forceinline__ void apply_u1_real(tv<R> (&a)[1 << RB], const cxf<R> (&m)[4],
-                                              const PhaseSet<R, RB> &pre, const PhaseSet<R, RB> &post)
-{
-    const R m0 = m[0].re, m1 = m[1].re, m2 = m[2].re, m3 = m[3].re;
-    cxf<R> m2w, m3w;
-    if constexpr (POST == 1) {
-        m2w = {m2 * post.w.re, m2 * post.w.im};
-        m3w = {m3 * post.w.re, m3 * post.w.im};
-    }
-#pragma unroll
-    for (int k = 0; k < (1 << (RB - 1)); ++k) {
-        const int r = pair_base<P>(k);
-        const int r1 = r | (1 << P);
-        cxf<R> x0 = cx<R>(a[r]), x1 = cx<R>(a[r1]);
-        cxf<R> y0, y1;
-        if constexpr (ZIN == 1) {
-            y0 = {m0 * x0.re, m0 * x0.im};
-            if constexpr (POST == 1) y1 = mul(m2w, x0);
-            else y1 = {m2 * x0.re, m2 * x0.im};
-        } else {
-            if constexpr (PRE > 0) x1 = mul(pair_phase<R, RB, P, PRE == 2>(pre, r), x1);
-            if constexpr (ZIN == 2) {
-                y0 = {m1 * x1.re, m1 * x1.im};
-                if constexpr (POST == 1) y1 = mul(m3w, x1);
-                else y1 = {m3 * x1.re, m3 * x1.im};
-            } else {
-                y0 = {m0 * x0.re + m1 * x1.re, m0 * x0.im + m1 * x1.im};
-                if constexpr (POST == 1) y1 = fma_c(m3w, x1, mul(m2w, x0));
-                else y1 = {m2 * x0.re + m3 * x1.re, m2 * x0.im + m3 * x1.im};
-            }
-        }
-        if constexpr (POST == 2) y1 = mul(pair_phase<R, RB, P, true>(post, r), y1);
-        a[r] = tvec(y0);
-        a[r1] = tvec(y1);
-    }
-}
-
-// A one-qubit update on a target that still holds its basis bit, with a real matrix and one
-// uniform output factor: one input of every pair is exactly zero (which one is the basis bit),
-// so their sum is the other; the |0> output is A times it (A real), the |1> output B times it.
-template <typename R, int RB, int P>
-__device__ __forceinline__ void apply_u1_untouched(tv<R> (&a)[1 << RB], R A, cxf<R> B)
-{
-#pragma unroll
-    for (int k = 0; k < (1 << (RB - 1)); ++k) {
-        const int r = pair_base<P>(k);
-        const int r1 = r | (1 << P);
-        const cxf<R> x = {a[r].x + a[r1].x, a[r].y + a[r1].y};
-        a[r] = tv<R>{A * x.re, A * x.im};
-        a[r1] = tvec(mul(B, x));
-    }
-}
-
-// REAL: the 4 x 4 matrix is real (a permutation, or the superoperator of a real Kraus set on
-// vec(rho)): two multiply-adds per product instead of four.
-template <typename R, int RB, int P0, int P1, bool REAL>
-__device__ __forceinline__ void apply_u2(tv<R> (&a)[1 << RB], const cxf<R> (&m)[16])
-{
-#pragma unroll
-    for (int k = 0; k < (1 << (RB - 2)); ++k) {
-        const int r0 = quad_base<P0, P1>(k);
-        const int r1 = r0 | (1 << P0), r2 = r0 | (1 << P1), r3 = r0 | (1 << P0) | (1 << P1);
-        const cxf<R> x0 = cx<R>(a[r0]), x1 = cx<R>(a[r1]), x2 = cx<R>(a[r2]), x3 = cx<R>(a[r3]);
-        cxf<R> y[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if constexpr (REAL) {
-                const R c0 = m[4 * i].re, c1 = m[4 * i + 1].re, c2 = m[4 * i + 2].re, c3 = m[4 * i + 3].re;
-                y[i] = {c0 * x0.re + c1 * x1.re + c2 * x2.re + c3 * x3.re,
-                        c0 * x0.im + c1 * x1.im + c2 * x2.im + c3 * x3.im};
-            } else {
-                cxf<R> s = mul(m[4 * i], x0);
-                s = fma_c(m[4 * i + 1], x1, s);
-                s = fma_c(m[4 * i + 2], x2, s);
-                s = fma_c(m[4 * i + 3], x3, s);
-                y[i] = s;
-            }
-        }
-        a[r0] = tvec(y[0]);
-        a[r1] = tvec(y[1]);
-        a[r2] = tvec(y[2]);
-        a[r3] = tvec(y[3]);
-    }
-}
-
-// Dispatch on the target register bit.  There is no pass-through branch (the last position
-// is the fall-back): every path rewrites the register tile, which lets the register allocator
-// keep the tile in the same registers across ops instead of copying it at each merge.
-template <typename R, int RB, int PRE, int POST, int ZIN>
-__device__ __forceinline__ void dispatch_u1_pp(int p, bool real, tv<R> (&a)[1 << RB], const cxf<R> (&m)[4],
-                                               const PhaseSet<R, RB> &pre, const PhaseSet<R, RB> &post)
-{
-    if (real) {
-        if (RB > 1 && p == 0) apply_u1_real<R, RB, 0, PRE, POST, ZIN>(a, m, pre, post);
-        else if (RB > 2 && p == 1) apply_u1_real<R, RB, 1 % RB, PRE, POST, ZIN>(a, m, pre, post);
-        else if (RB > 3 && p == 2) apply_u1_real<R, RB, 2 % RB, PRE, POST, ZIN>(a, m, pre, post);
-        else apply_u1_real<R, RB, RB - 1, PRE, POST, ZIN>(a, m, pre, post);
-        return;
-    }
-    if (RB > 1 && p == 0) apply_u1<R, RB, 0, PRE, POST, ZIN>(a, m, pre, post);
-    else if (RB > 2 && p == 1) apply_u1<R, RB, 1 % RB, PRE, POST, ZIN>(a, m, pre, post);
-    else if (RB > 3 && p == 2) apply_u1<R, RB, 2 % RB, PRE, POST, ZIN>(a, m, pre, post);
-    else apply_u1<R, RB, RB - 1, PRE, POST, ZIN>(a, m, pre, post);
-}
-
-// zin: 0 general, 1 the |1> inputs are zero (no input phase to apply), 2 the |0> inputs are zero.
-// postkind: 0 no output block, 1 one factor per thread, 2 with register-bit factors.
-template <typename R, int RB, int PRE, int ZIN>
-__device__ __forceinline__ void dispatch_u1_post(int p, bool real, int postkind, tv<R> (&a)[1 << RB],
-                                                 const cxf<R> (&m)[4], const PhaseSet<R, RB> &pre,
-                                                 const PhaseSet<R, RB> &post)
-{
-    if (postkind == 2) dispatch_u1_pp<R, RB, PRE, 2, ZIN>(p, real, a, m, pre, post);
-    else if (postkind == 1) dispatch_u1_pp<R, RB, PRE, 1, ZIN>(p, real, a, m, pre, post);
-    else dispatch_u1_pp<R, RB, PRE, 0, ZIN>(p, real, a, m, pre, post);
-}
-
-template <typename R, int RB>
-__device__ __forceinline__ void dispatch_u1(int p, bool real, int prekind, int zin, int postkind,
-                                            tv<R> (&a)[1 << RB], const cxf<R> (&m)[4],
-                                            const PhaseSet<R, RB> &pre, const PhaseSet<R, RB> &post)
-{
-    if (zin == 1) {
-        dispatch_u1_post<R, RB, 0, 1>(p, real, postkind, a, m, pre, post);
-    } else if (zin == 2) {
-        if (prekind == 2) dispatch_u1_post<R, RB, 2, 2>(p, real, postkind, a, m, pre, post);
-        else if (prekind == 1) dispatch_u1_post<R, RB, 1, 2>(p, real, postkind, a, m, pre, post);
-        else dispatch_u1_post<R, RB, 0, 2>(p, real, postkind, a, m, pre, post);
-    } else if (prekind == 2) {
-        dispatch_u1_post<R, RB, 2, 0>(p, real, postkind, a, m, pre, post);
-    } else if (prekind == 1) {
-        dispatch_u1_post<R, RB, 1, 0>(p, real, postkind, a, m, pre, post);
-    } else {
-        dispatch_u1_post<R, RB, 0, 0>(p, real, postkind, a, m, pre, post);
-    }
-}
-
-template <typename R, int RB, bool REAL>
-__device__ __forceinline__ void dispatch_u2_t(int p0, int p1, tv<R> (&a)[1 << RB], const cxf<R> (&m)[16])
-{
-    if constexpr (RB >= 2) {
-        switch (p0 * 4 + p1) {
-#define QS_U2_CASE(A, B) \
-    case (A) * 4 + (B): if constexpr ((A) < RB && (B) < RB) apply_u2<R, RB, (A) % RB, (B) % RB, REAL>(a, m); break;
-        QS_U2_CASE(0, 1) QS_U2_CASE(1, 0) QS_U2_CASE(0, 2) QS_U2_CASE(2, 0)
-        QS_U2_CASE(0, 3) QS_U2_CASE(3, 0) QS_U2_CASE(1, 2) QS_U2_CASE(2, 1)
-        QS_U2_CASE(1, 3) QS_U2_CASE(3, 1) QS_U2_CASE(2, 3) QS_U2_CASE(3, 2)
-#undef QS_U2_CASE
-        default: break;
-        }
-    }
-}
-
-template <typename R, int RB>
-__device__ __forceinline__ void dispatch_u2(int p0, int p1, bool real, tv<R> (&a)[1 << RB], const cxf<R> (&m)[16])
-{
-    if (real) dispatch_u2_t<R, RB, true>(p0, p1, a, m);
-    else dispatch_u2_t<R, RB, false>(p0, p1, a, m);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -462,55 +199,66 @@ __global__ void k_block_prep(int S, int round_begin, int n_rounds, int rec_size,
 }
 
 // ---------------------------------------------------------------------------------------
-// Phase chains (one thread per chain and slot, FP64).  Along a chain of one-qubit gates on
-// one wire, each inner gate's matrix M (with the phase carried from the gate before it
+// Phase chains (one wave per chain and slot, FP64).  Along a chain of one-qubit gates on
+// one wire, each inner gate's matrix M (with the phase c carried from the gate before it
 // multiplied into its |1> column) is factored as M = p * diag(1, b) * Rm * diag(1, d) with
 // unit p, b, d and Rm real.  Its row is rewritten as Rm in words 0, 2, 4, 6 and the input
 // phase d in words 1, 3; b is carried to the next gate, p into the global phase, which the
 // last gate of the chain takes along with the carried b (its row stays a complex matrix).
-// The factors: p = phase(M00), d = phase(M01) / p, and b from the larger of the second row's
-// entries, phase(M11) / (p d) or -phase(M10) / p; Rm is the real part of M with those phases
+// The factors: p = phase(M00), d = c phase(M01) / p, and b from the larger of the second row's
+// entries, phase(M11) / phase(M01) or -phase(M10) / p; Rm is the real part of M with those phases
 // divided out.  For a unitary M (M10 = -e^{it} conj(M01), M11 = e^{it} conj(M00)) the
 // divided-out entries are real, so the factors reproduce M; a phase taken from a zero or
 // rounding-sized entry only affects entries of that size.  (phase(0) = 1.)
+// c drops out of b, so the lanes factor 64 gates at once, take c from the lane before and multiply
+// the global phase in a tree (60 gates: 74 us as one thread's walk, CXTIME here).
 // ---------------------------------------------------------------------------------------
-__global__ void k_phase_chains(double *tab, int S, const int32_t *chain_gates, const int32_t *chain_off,
-                               int n_chains)
+__global__ void __launch_bounds__(256) k_phase_chains(double *tab, int S, const int32_t *__restrict__ chain_gates,
+                                                      const int32_t *__restrict__ chain_off, int n_chains)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= (int64_t)n_chains * S) return;
+    const int lane = (int)(threadIdx.x & 63u);
     const int c = (int)(i / S), s = (int)(i % S);
     const int kb = chain_off[c], ke = chain_off[c + 1];
-    double2 carry = make_double2(1.0, 0.0), glob = make_double2(1.0, 0.0);
-    for (int k = kb; k < ke; ++k) {
-        double *t = tab + ((int64_t)chain_gates[k] * S + s) * 8;
-        const double2 m00 = make_double2(t[0], t[1]), m10 = make_double2(t[4], t[5]);
-        const double2 m01 = dmul(make_double2(t[2], t[3]), carry);
-        const double2 m11 = dmul(make_double2(t[6], t[7]), carry);
-        if (k == ke - 1) {
-            const double2 o[4] = {dmul(glob, m00), dmul(glob, m01), dmul(glob, m10), dmul(glob, m11)};
+    const double2 one = make_double2(1.0, 0.0);
+    double2 carry = one, glob = one;
+    for (int k0 = kb; k0 < ke; k0 += 64) {
+        const int k = k0 + lane;
+        const bool in = k < ke, inner = k < ke - 1;
+        double *t = tab + ((int64_t)chain_gates[in ? k : ke - 1] * S + s) * 8;
+        const double2 m00 = make_double2(t[0], t[1]), m01 = make_double2(t[2], t[3]);
+        const double2 m10 = make_double2(t[4], t[5]), m11 = make_double2(t[6], t[7]);
+        const double2 p = dunit(m00), q = dunit(m01);
+        const double2 b = hypot(m11.x, m11.y) >= hypot(m10.x, m10.y)
+                              ? dmul(dunit(m11), dconj(q))
+                              : dmul(make_double2(-1.0, 0.0), dmul(dunit(m10), dconj(p)));
+        double2 cin = make_double2(__shfl_up(b.x, 1, 64), __shfl_up(b.y, 1, 64));
+        if (lane == 0) cin = carry;
+        double2 g = inner ? p : one;
+        for (int off = 32; off > 0; off >>= 1)
+            g = dmul(g, make_double2(__shfl_xor(g.x, off, 64), __shfl_xor(g.y, off, 64)));
+        glob = dmul(glob, g);
+        if (inner) {
+            const double2 d = dmul(cin, dmul(q, dconj(p))), pb = dmul(p, b);
+            t[0] = dmul(m00, dconj(p)).x;
+            t[2] = dmul(m01, dconj(q)).x;
+            t[4] = dmul(m10, dconj(pb)).x;
+            t[6] = dmul(m11, dconj(dmul(q, b))).x;
+            t[1] = d.x;
+            t[3] = d.y;
+            t[5] = 0.0;
+            t[7] = 0.0;
+        } else if (in) {
+            // the last gate: its chunk is the last one, so glob is complete
+            const double2 gc = dmul(glob, cin);
+            const double2 o[4] = {dmul(glob, m00), dmul(gc, m01), dmul(glob, m10), dmul(gc, m11)};
             for (int j = 0; j < 4; ++j) {
                 t[2 * j] = o[j].x;
                 t[2 * j + 1] = o[j].y;
             }
-            break;
         }
-        const double2 p = dunit(m00);
-        const double2 d = dmul(dunit(m01), dconj(p));
-        const double2 b = hypot(m11.x, m11.y) >= hypot(m10.x, m10.y)
-                              ? dmul(dunit(m11), dconj(dmul(p, d)))
-                              : dmul(make_double2(-1.0, 0.0), dmul(dunit(m10), dconj(p)));
-        const double2 pb = dmul(p, b), pd = dmul(p, d);
-        t[0] = dmul(m00, dconj(p)).x;
-        t[2] = dmul(m01, dconj(pd)).x;
-        t[4] = dmul(m10, dconj(pb)).x;
-        t[6] = dmul(m11, dconj(dmul(pb, d))).x;
-        t[1] = d.x;
-        t[3] = d.y;
-        t[5] = 0.0;
-        t[7] = 0.0;
-        carry = b;
-        glob = dmul(glob, p);
+        carry = make_double2(__shfl(b.x, 63, 64), __shfl(b.y, 63, 64));
     }
 }
 
@@ -520,8 +268,8 @@ hipError_t launch_phase_chains(double *tab, int S, const int32_t *chain_gates, c
     const int64_t tot = (int64_t)n_chains * S;
     if (tot <= 0) return hipSuccess;
     TimedLaunch tl("chains", (double)tot * 64.0, st);
-    hipLaunchKernelGGL(k_phase_chains, dim3((unsigned)((tot + 127) / 128)), dim3(128), 0, st, tab, S,
-                       chain_gates, chain_off, n_chains);
+    hipLaunchKernelGGL(k_phase_chains, dim3((unsigned)((tot + 3) / 4)), dim3(256), 0, st, tab, S, chain_gates, chain_off,
+                       n_chains);
     return hipGetLastError();
 }
 
@@ -598,10 +346,10 @@ __global__ void k_pass_prep(int S, int op_begin, int n_ops, int rec_size, Progra
         for (int post = 0; post < 2; ++post) {
             int block = post ? op.post_rec : op.pre_rec;
             if (block < 0) continue;
-            double2 preg[kMaxRegBits], ptid[9];
+            double2 preg[kMaxRegBits], ptid[10];
             double2 ubas = make_double2(1.0, 0.0);     // the block's basis-conditioned factors
             for (int k = 0; k < kMaxRegBits; ++k) preg[k] = make_double2(1.0, 0.0);
-            for (int k = 0; k < 9; ++k) ptid[k] = make_double2(1.0, 0.0);
+            for (int k = 0; k < 10; ++k) ptid[k] = make_double2(1.0, 0.0);
             for (int k = op.pref_begin; k < op.pref_end; ++k) {
                 const PrepRef pr = prog.prefs[k];
                 if (pr.post != post) continue;
@@ -626,6 +374,8 @@ __global__ void k_pass_prep(int S, int op_begin, int n_ops, int rec_size, Progra
                     if ((y >> k) & 1) w = dmul(w, ptid[5 + k]);
                 put(b + 36 + y, w);
             }
+            put(b + 52, make_double2(1.0, 0.0));
+            put(b + 53, ptid[9]);
         }
     } else if (op.type == OP_U2) {
         const double *m = gates[op.gate].m;
@@ -1385,6 +1135,7 @@ hipError_t launch_fused_pass(void *psi, qs_dtype dt, int n, int S, const PassDes
                              double *ovl, int slot_base, int slots)
 {
     const PassDesc &h = *pass_host;
+    if (h.state) return hipErrorInvalidValue;   // launch_state_pass
     if (h.expand)
         return launch_expand_pass(psi, dt, n, S, pass_host, pass_index, init, basis, prog, rec, wtab, otab, st, dyn, ovl,
                                   slot_base, slots);

@@ -39,11 +39,12 @@ void clear_error();
 //   reg[RB]  phase factor per register bit,
 //   lo[32]   product over the thread-id bits 0..4 that are set, indexed by tid & 31,
 //   hi[16]   product over the thread-id bits 5..8 that are set, indexed by tid >> 5,
+//   top[2]   the factor of thread-id bit 9 (workgroups of 1024 threads only),
 //   outer[n] the phases conditioned on tile-number bits (multiplied per tile in the kernel).
 // ---------------------------------------------------------------------------------------
 constexpr int kMaxTileBits = 15;
 constexpr int kMaxRegBits = 4;
-constexpr int kPhaseTable = 4 + 32 + 16;   // reg + lo + hi entries of a phase block
+constexpr int kPhaseTable = 4 + 32 + 16 + 2;   // reg + lo + hi + top entries of a phase block
 
 struct RoundDesc {
     uint32_t reg_mask;            // tile-local bits held in registers during this round
@@ -111,6 +112,8 @@ struct PassDesc {
     int32_t mixed_ops;            // the pass has ops other than one-qubit gates
     int32_t expand;               // zin_ops 3 with enough targets: the pass is the product of its
                                   // targets' factors (see k_expand) and runs as one
+    int32_t state;                // the tile is the whole state: the program runs as StateOps (2:
+                                  // every one-qubit op real without phases, no two-qubit op)
     int16_t xop[16];              // expand: op (relative to op_begin) of tile-local bit j, -1 none
 };
 
@@ -130,9 +133,11 @@ struct StageDesc {
     int32_t rec_begin, rec_end;
     int32_t job_begin, job_end;   // absolute OuterJob indices
     int32_t obits_begin, obits_end;
+    int32_t sop_begin, sop_end;   // whole-state programs: the stage's StateOps (absolute)
 };
 
 constexpr int kStageOps = 48;     // op descriptors per stage
+constexpr int kStageSops = kStageOps;   // StateOps per stage, at most one per op
 constexpr int kStageJobs = 64;    // outer jobs per stage
 constexpr int kStageObits = 512;  // outer condition bits per stage
 
@@ -171,6 +176,20 @@ struct OpDesc {
     // this op (they still hold the run's basis bits, so registers that disagree there are zero)
     uint32_t creg;
     uint64_t omask, ovalue;       // DIAG: tile condition (outer index & omask) == ovalue
+};
+
+// One step of a whole-state program (k_state).  First an exchange into the register layout `to`
+// (0: none), then by kind (low two bits of code): one-qubit ops on register bits 0, 1, ... in
+// ascending order (those of the mask code >> 2), a dense two-qubit op on register bits (code >> 2,
+// code >> 4), or a diagonal pattern (tile-local index & a) == b.  op[p]: record entry | input block
+// << 16, and output block | SOP flags << 16 (input phase kind in the low two bits, output phase kind
+// in the next: 0 none, 1 one factor per thread, 2 with register-bit factors), all entries relative to
+// the stage.  U2 and DIAG take op[0].
+constexpr uint32_t SOP_SEQ = 0, SOP_U2 = 1, SOP_DIAG = 2;
+constexpr uint32_t SOP_REAL = 16, SOP_PRE_UNI = 32, SOP_POST_UNI = 64;
+struct StateOp {
+    uint32_t code, to, a, b;
+    uint32_t op[4][2];
 };
 
 // A controlled phase folded into a one-qubit op: the phase of gate `gate` (noise table) when
@@ -281,6 +300,7 @@ struct ProgramDev {
     const PrepRef *prefs;
     const OuterJob *jobs;
     const int32_t *obits;
+    const StateOp *sops;
 };
 
 // Records of pass `pass_host` for all S slots into rec (S * rec_size complex entries).
@@ -313,6 +333,14 @@ hipError_t launch_expand_pass(void *psi, qs_dtype dt, int n, int S, const PassDe
                               int64_t init, int64_t basis, ProgramDev prog, const void *rec, const void *wtab,
                               const uint64_t *otab, hipStream_t st, const RunParams *dyn, double *ovl, int slot_base,
                               int slots);
+// The whole program of a state that fits one tile (PassDesc::state), one workgroup per slot, from
+// the basis state |init>.  state_shape: whether 2^n amplitudes with 2^RB per thread run so;
+// state_reg_bits: the register bits of the automatic plan (0: the state does not fit).
+hipError_t launch_state_pass(void *psi, qs_dtype dt, int n, int S, const PassDesc *pass_host, int pass_index,
+                             int64_t init, ProgramDev prog, const void *rec, hipStream_t st, const RunParams *dyn);
+bool state_shape(qs_dtype dt, int n, int RB);
+int state_reg_bits(qs_dtype dt, int n);
+hipError_t state_prepare_attributes();
 // Walked tile-number bits of a pass launch (the tiles its blocks cover).
 int fused_walked_bits(int n, const PassDesc *pass_host, int64_t init);
 // Overlap partials per slot of a pass launched with ovl: 2^(these bits).
@@ -369,6 +397,7 @@ struct Program {
     std::vector<PrepRef> prefs;
     std::vector<OuterJob> jobs;
     std::vector<int32_t> obits;
+    std::vector<StateOp> sops;    // whole-state programs
     std::vector<int32_t> layout;  // logical qubit -> physical bit after the circuit
     // Phase chains: chain c is gates chain_gates[chain_off[c] .. chain_off[c + 1]), in circuit
     // order (empty: no chains; otherwise chain_off has one entry per chain plus one).
@@ -380,8 +409,9 @@ struct Program {
 
 // mfma: run eligible register rounds as dense blocks on the matrix cores (RB = 4 only); phase
 // chains are then not formed.
+// state: the tile is the whole state and runs as a StateOp program.
 qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, int run_bits,
-                     int rec_cap, Program &out, bool mfma = false);
+                     int rec_cap, Program &out, bool mfma = false, bool state = false);
 
 // Complex entries of one block round's operand table per slot (1024 floats).
 constexpr int kBlockRecEntries = 512;

@@ -222,15 +222,16 @@ int find_pos(const std::vector<int> &v, int x)
 }  // namespace
 
 qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, int run_bits,
-                     int rec_cap, Program &P, bool mfma)
+                     int rec_cap, Program &P, bool mfma, bool state)
 {
     if (K > n) K = n;
     if (K > kMaxTileBits) K = kMaxTileBits;
     if (RB > K) RB = K;
     if (RB > kMaxRegBits) RB = kMaxRegBits;
     if (K < 1 || RB < 1) return fail(QS_EINVAL, "fused plan: tile and register bits must be >= 1");
-    if (K - RB > 9) return fail(QS_EINVAL, "fused plan: at most 512 threads per tile (tile_bits - reg_bits <= 9)");
-    if (RB == 4 && K - RB > 8)
+    if (state && K != n) return fail(QS_EINVAL, "fused plan: a whole-state program needs one tile");
+    if (!state && K - RB > 9) return fail(QS_EINVAL, "fused plan: at most 512 threads per tile (tile_bits - reg_bits <= 9)");
+    if (!state && RB == 4 && K - RB > 8)
         return fail(QS_EINVAL, "fused plan: reg_bits 4 allows at most 256 threads per tile (tile_bits <= 12)");
     const bool whole = (n == K);
     int max_targets = whole ? K : K - run_bits;
@@ -786,6 +787,56 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
         }
         pd.stage_end = (int)P.stages.size();
         pd.round_end = (int)P.rounds.size();
+        if (state) {
+            // the program as StateOps: runs of one-qubit ops on ascending register bits, and the
+            // other ops, with the exchange that opens a round on its first step
+            uint32_t cur = P.rounds[pd.round_begin].reg_mask;
+            for (int si = pd.stage_begin; si < pd.stage_end; ++si) {
+                StageDesc &sd = P.stages[si];
+                sd.sop_begin = (int)P.sops.size();
+                for (int ri = sd.round_begin; ri < sd.round_end; ++ri) {
+                    const RoundDesc &rd = P.rounds[ri];
+                    int last = RB;   // register bit of the open run's last op (RB: no open run)
+                    for (int oi = rd.op_begin; oi < rd.op_end; ++oi) {
+                        const OpDesc &o = P.ops[oi];
+                        const bool u1 = o.type == OP_U1;
+                        if (!u1 || last >= o.p0) {
+                            StateOp x{};
+                            x.code = u1 ? SOP_SEQ : o.type == OP_U2 ? SOP_U2 : SOP_DIAG;
+                            if (rd.reg_mask != cur) x.to = cur = rd.reg_mask;
+                            P.sops.push_back(x);
+                        }
+                        last = u1 ? o.p0 : RB;
+                        StateOp &x = P.sops.back();
+                        uint32_t pre = 0, post = 0, fl = (o.flags & OPF_REAL) ? SOP_REAL : 0;
+                        if (u1) {
+                            x.code |= 4u << o.p0;
+                            if (o.flags & OPF_UPHASE) {
+                                // the uniform entry rec + 4, read as a block's entry 4
+                                fl |= 1u | SOP_PRE_UNI;
+                                pre = (uint32_t)(o.rec - sd.rec_begin);
+                            } else if (o.pre_rec >= 0) {
+                                fl |= ((o.flags & OPF_PREW) ? 1u : 2u) | ((o.flags & OPF_PRE_UNI) ? SOP_PRE_UNI : 0u);
+                                pre = (uint32_t)(o.pre_rec - sd.rec_begin);
+                            }
+                            if (o.post_rec >= 0) {
+                                fl |= ((o.flags & OPF_POSTW) ? 4u : 8u) | ((o.flags & OPF_POST_UNI) ? SOP_POST_UNI : 0u);
+                                post = (uint32_t)(o.post_rec - sd.rec_begin);
+                            }
+                        } else if (o.type == OP_U2) {
+                            x.code |= (uint32_t)o.p0 << 2 | (uint32_t)o.p1 << 4;
+                        } else {
+                            x.a = o.lmask;
+                            x.b = o.lvalue;
+                        }
+                        const int k = u1 ? o.p0 : 0;
+                        x.op[k][0] = (uint32_t)(o.rec - sd.rec_begin) | pre << 16;
+                        x.op[k][1] = post | fl << 16;
+                    }
+                }
+                sd.sop_end = (int)P.sops.size();
+            }
+        }
         pd.store_round = st_mask == io_mask ? pd.load_round : pd.round_end - 1;
         // a pass runs its rounds either all as blocks or all op by op (the kernel variants)
         {
@@ -866,6 +917,15 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
         // as an expansion when four targets lie above the four lowest tile-local bits (registers;
         // the lanes keep rows of at least 16 amplitudes) and the tile gives whole waves of threads.
         for (int j = 0; j < 16; ++j) pd.xop[j] = -1;
+        if (state) {
+            pd.state = 2;
+            for (int oi = pd.op_begin; oi < (int)P.ops.size(); ++oi) {
+                const OpDesc &o = P.ops[oi];
+                if (o.type == OP_U2 || (o.type == OP_U1 && (!(o.flags & OPF_REAL) || (o.flags & OPF_CHAIN) ||
+                                                            o.pre_rec >= 0 || o.post_rec >= 0)))
+                    pd.state = 1;
+            }
+        }
         if (pd.zin_ops == 3 && K >= 10 && K <= 12 && Q[0] == 0) {
             int high = 0;
             for (int oi = pd.op_begin; oi < (int)P.ops.size(); ++oi) {
@@ -873,8 +933,8 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                 pd.xop[j] = (int16_t)(oi - pd.op_begin);
                 high += j >= 4;
             }
-            pd.expand = high >= kExpandRegs;
-            if (pd.expand) rec = std::max(rec, 2 * K);   // its records start with 2 K factors
+            pd.expand = high >= kExpandRegs && rec >= 2 * K;   // its records start with 2 K factors
+            if (pd.expand) pd.state = 0;
         }
         pd.op_end = (int)P.ops.size();
         pd.job_end = (int)P.jobs.size();
