@@ -121,6 +121,7 @@ struct qs_fr_s {
     double *scratch;     // device: gram partials | gram out | coef | overlap partials | out | table
     size_t off_gram, off_coef, off_ovp, off_ovo, off_tab;
     double *host;        // pinned staging: gram, then coef (kFrHostGram doubles each)
+    double *host_dev;    // its device address (the Gram's final sum writes there)
 };
 
 // Doubles of one Gram or coefficient matrix: 32 x 32 complex (two-qubit Kraus sets; a
@@ -1842,6 +1843,13 @@ qs_status qs_fr_create(int n, int r, qs_dtype dt, void *buf, size_t bytes, void 
         delete f;
         return hip_fail(e, "fr_create: hipHostMalloc staging");
     }
+    e = hipHostGetDevicePointer((void **)&f->host_dev, f->host, 0);
+    if (e != hipSuccess) {
+        (void)hipFree(f->scratch);
+        (void)hipHostFree(f->host);
+        delete f;
+        return hip_fail(e, "fr_create: device address of the staging");
+    }
     *out = f;
     return QS_OK;
 }
@@ -1889,14 +1897,20 @@ static qs_status fr_kraus_step(qs_fr f, int k, const int32_t *qb, int n_ops, con
     const int d = 1 << k;            // operator dimension
     const int G = d * 8;             // sub-columns of the Gram matrix (column c < rank at x * 8 + c)
     const int rin = f->rank;
-    double *gram_dev = f->scratch + f->off_gram;
-    if (k == 1) QS_HIP(launch_fr_gram(f->V, f->dt, f->n, rin, qb[0], f->scratch, gram_dev, f->st));
-    else QS_HIP(launch_fr_gram2(f->V, f->dt, f->n, rin, qb[0], qb[1], f->scratch, gram_dev, f->st));
-    QS_HIP(hipMemcpyAsync(f->host, gram_dev, (size_t)G * G * 2 * sizeof(double), hipMemcpyDeviceToHost, f->st));
+    // two-qubit sets of diagonal operators (a noisy controlled phase) use only the Gram entries
+    // with equal x and mix each quarter's columns among themselves: compact 8-column matrices
+    bool diag = k == 2;
+    for (int a = 0; diag && a < n_ops; ++a)
+        for (int i = 0; i < 16; ++i)
+            if (i % 5 != 0 && (ops[32 * a + 2 * i] != 0.0 || ops[32 * a + 2 * i + 1] != 0.0)) diag = false;
+    const int W = diag ? 8 : G;      // row length of the Gram and coefficient matrices
+    // the final sum writes the matrix to the pinned host buffer, so no copy follows it
+    if (k == 1) QS_HIP(launch_fr_gram(f->V, f->dt, f->n, rin, qb[0], f->scratch, f->host_dev, f->st));
+    else QS_HIP(launch_fr_gram2(f->V, f->dt, f->n, rin, qb[0], qb[1], diag, f->scratch, f->host_dev, f->st));
     QS_HIP(hipStreamSynchronize(f->st));
-    // Gamma[(x, c), (y, d)] at index (x * 8 + c) * G + (y * 8 + d)
+    // Gamma[(x, c), (y, d)] at row x * 8 + c, column y * 8 + d (compact: d, equal x and y only)
     auto Gam = [&](int x, int c, int y, int dd) {
-        size_t i = (size_t)(x * 8 + c) * G + (y * 8 + dd);
+        size_t i = (size_t)(x * 8 + c) * W + (diag ? dd : y * 8 + dd);
         return cd(f->host[2 * i], f->host[2 * i + 1]);
     };
     const int dd2 = d * d;
@@ -1919,7 +1933,8 @@ static qs_status fr_kraus_step(qs_fr f, int k, const int32_t *qb, int n_ops, con
                 for (int e2 = 0; e2 < rin; ++e2) {
                     cd acc = 0;
                     for (int x = 0; x < d; ++x)
-                        for (int y = 0; y < d; ++y) acc += C[(size_t)x * d + y] * Gam(x, c, y, e2);
+                        for (int y = diag ? x : 0; y < (diag ? x + 1 : d); ++y)
+                            acc += C[(size_t)x * d + y] * Gam(x, c, y, e2);
                     GW[(size_t)(a * rin + c) * m + (b * rin + e2)] = acc;
                 }
         }
@@ -1943,23 +1958,23 @@ static qs_status fr_kraus_step(qs_fr f, int k, const int32_t *qb, int n_ops, con
     const double scale = 1.0 / std::sqrt(kept);
     // coef[(x' * 8 + k'), (y * 8 + c)] = sum_a Q[(a, c), k'] E_a[x'][y] / sqrt(kept)
     double *coef = f->host + kFrHostGram;
-    std::memset(coef, 0, (size_t)G * G * 2 * sizeof(double));
+    std::memset(coef, 0, (size_t)G * W * 2 * sizeof(double));
     for (int xo = 0; xo < d; ++xo)
         for (int ko = 0; ko < keep; ++ko)
-            for (int y = 0; y < d; ++y)
+            for (int y = diag ? xo : 0; y < (diag ? xo + 1 : d); ++y)
                 for (int c = 0; c < rin; ++c) {
                     cd acc = 0;
                     for (int a = 0; a < n_ops; ++a) acc += Q[(size_t)(a * rin + c) * m + order[ko]] * E(a, xo, y);
                     acc *= scale;
-                    size_t i = (size_t)(xo * 8 + ko) * G + (y * 8 + c);
+                    size_t i = (size_t)(xo * 8 + ko) * W + (diag ? c : y * 8 + c);
                     coef[2 * i] = acc.real();
                     coef[2 * i + 1] = acc.imag();
                 }
     double *coef_dev = f->scratch + f->off_coef;
-    QS_HIP(hipMemcpyAsync(coef_dev, coef, (size_t)G * G * 2 * sizeof(double), hipMemcpyHostToDevice, f->st));
+    QS_HIP(hipMemcpyAsync(coef_dev, coef, (size_t)G * W * 2 * sizeof(double), hipMemcpyHostToDevice, f->st));
     if (k == 1) QS_HIP(launch_fr_recombine(f->V, f->dt, f->n, rin, keep, qb[0], coef_dev, f->st));
-    else QS_HIP(launch_fr_recombine2(f->V, f->dt, f->n, rin, keep, qb[0], qb[1], coef_dev, f->st));
-    // the staging buffer is next written after the next step's synchronisation, which orders it
+    else QS_HIP(launch_fr_recombine2(f->V, f->dt, f->n, rin, keep, qb[0], qb[1], diag, coef_dev, f->st));
+    // the coefficients are next written after the next step's synchronisation, which orders it
     // after this upload
     f->rank = keep;
     f->log_trace += std::log(kept);

@@ -211,7 +211,7 @@ __global__ void k_block_prep(int S, int round_begin, int n_rounds, int rec_size,
 // divided-out entries are real, so the factors reproduce M; a phase taken from a zero or
 // rounding-sized entry only affects entries of that size.  (phase(0) = 1.)
 // c drops out of b, so the lanes factor 64 gates at once, take c from the lane before and multiply
-// the global phase in a tree (60 gates: 74 us as one thread's walk, CXTIME here).
+// the global phase in a tree (60 gates: 74 us as one thread's walk, 4 us here).
 // ---------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_phase_chains(double *tab, int S, const int32_t *__restrict__ chain_gates,
                                                       const int32_t *__restrict__ chain_off, int n_chains)

@@ -367,10 +367,11 @@ hipError_t launch_fr_recombine(void *V, qs_dtype dt, int n, int r_in, int r_out,
                                const double *coef_dev, hipStream_t st);
 // Two-qubit Kraus sets: Gram of the 4r quarter-columns on (q0, q1) (32 x 32 complex, entry
 // (x * 8 + c, y * 8 + d) with x = bit q0 + 2 bit q1) and the recombination with a 32 x 32
-// coefficient matrix.
-hipError_t launch_fr_gram2(const void *V, qs_dtype dt, int n, int r, int q0, int q1, double *partials,
+// coefficient matrix.  diag: every operator is diagonal, and only the entries with equal x are
+// formed and used, in the compact layout (x * 8 + c) * 8 + d (gram) and (x * 8 + k') * 8 + c (coef).
+hipError_t launch_fr_gram2(const void *V, qs_dtype dt, int n, int r, int q0, int q1, bool diag, double *partials,
                            double *gram_out, hipStream_t st);
-hipError_t launch_fr_recombine2(void *V, qs_dtype dt, int n, int r_in, int r_out, int q0, int q1,
+hipError_t launch_fr_recombine2(void *V, qs_dtype dt, int n, int r_in, int r_out, int q0, int q1, bool diag,
                                 const double *coef_dev, hipStream_t st);
 
 // ---------------------------------------------------------------------------------------
