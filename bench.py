@@ -36,7 +36,7 @@ def log(msg):
 
 def source_hash():
     h = hashlib.sha256()
-    for f in ("fused.hip", "planner.cpp"):
+    for f in ("fused.hip", "fused_kernel.h", "expand.hip", "planner.cpp"):
         with open(os.path.join(ROOT, "paper_1412_2293_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -13,7 +13,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqsim.so")
 
-SOURCES = ["kernels.hip", "fused.hip", "expand.hip", "state.hip", "fr.hip", "noalloc.hip", "api.cpp", "planner.cpp", "serve.cpp"]
+SOURCES = ["kernels.hip", "fused.hip", "fused_c64.hip", "fused_c128.hip", "expand.hip", "state.hip", "fr.hip", "noalloc.hip", "api.cpp", "planner.cpp", "serve.cpp"]
 ARCH = "gfx950"
 
 

@@ -577,13 +577,15 @@ qs_status fused_plan_for(const qs_gate *gates, int n_gates, int n, qs_dtype dt, 
     if ((size_t(1) << std::min(K, n)) * amp_bytes(dt) > 160 * 1024)
         return fail(QS_EINVAL, "plan: tile does not fit the 160 KiB LDS of a gfx950 CU");
     if (RB > kMaxRegBits) return fail(QS_EINVAL, "plan: reg_bits must be <= 4");
+    const bool exact = K == n;
     if (n <= K) {
         K = n;   // the whole state is one tile: the circuit runs as one launch
         if (RB > K) RB = K;
     }
     const bool state = K == n && !mfma && state_shape(dt, n, RB);
     // wide register tiles (16 complex<float>, 8 or 16 complex<double>) run 256-thread blocks
-    if (!state && (RB == 4 || (dt == QS_C128 && RB == 3)) && K - RB > 8)
+    // (more only in the shape that the automatic plan gives a whole-state program, given as such)
+    if (!(state && exact && RB == state_reg_bits(dt, n)) && (RB == 4 || (dt == QS_C128 && RB == 3)) && K - RB > 8)
         return fail(QS_EINVAL, "plan: this register tile allows at most 256 threads (tile_bits - reg_bits <= 8)");
     out.K = K;
     out.RB = RB;
@@ -1221,7 +1223,7 @@ qs_status qs_plan_describe(const qs_gate *gates, int n_gates, int n, qs_dtype dt
     I("RB", pl.prog.RB);
     I("mfma", pl.mfma ? 1 : 0);
     I("run_bits", pl.run_bits);
-    if (pl.fused) I("stage_rec_cap", stage_rec_cap(dt, pl.prog.K));
+    if (pl.fused) I("stage_rec_cap", stage_rec_area(dt, pl.prog.K));
     {
         const double cost = pl.fused ? model_cost_fused(pl.prog, n, dt, kModelSlots, pl.run_bits)
                                      : model_cost_unfused(gates, n_gates, n, dt, kModelSlots);
@@ -1255,6 +1257,7 @@ qs_status qs_plan_describe(const qs_gate *gates, int n_gates, int n, qs_dtype dt
         I("mixed_ops", pd.mixed_ops);
         I("expand", pd.expand);
         I("state", pd.state);
+        I("shear", pd.shear);
         I("rec_size", pd.rec_size);
         I("load_round", pd.load_round);
         I("load_reg_mask", P.rounds[pd.load_round].reg_mask);

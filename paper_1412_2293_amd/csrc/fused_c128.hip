@@ -1,0 +1,12 @@
+// The fused pass kernels for complex<double> (one file per amplitude type, so that they compile side by
+// side).
+#include "fused_kernel.h"
+
+namespace qs {
+
+template hipError_t fused_attributes<double>();
+template hipError_t fused_launch<double>(double *, int, int, const PassDesc &, int, int, int64_t, int64_t, const RunParams *,
+                                      ProgramDev, const void *, const void *, const uint64_t *, size_t, hipStream_t,
+                                      double *, int, int);
+
+}  // namespace qs

@@ -109,11 +109,12 @@ struct PassDesc {
                                   // 3 all, each with a real matrix, no input phase and at most
                                   // a uniform output factor; 4 none, each with a real matrix and
                                   // no folded phase; 5 the pass has no one-qubit op
+    int32_t shear;                // zin_ops 4, and every one-qubit op runs sheared (OPF_SHEAR)
     int32_t mixed_ops;            // the pass has ops other than one-qubit gates
     int32_t expand;               // zin_ops 3 with enough targets: the pass is the product of its
                                   // targets' factors (see k_expand) and runs as one
     int32_t state;                // the tile is the whole state: the program runs as StateOps (2:
-                                  // every one-qubit op real without phases, no two-qubit op)
+                                  // every one-qubit op a sheared one without phases, no two-qubit op)
     int16_t xop[16];              // expand: op (relative to op_begin) of tile-local bit j, -1 none
 };
 
@@ -133,6 +134,8 @@ struct StageDesc {
     int32_t rec_begin, rec_end;
     int32_t job_begin, job_end;   // absolute OuterJob indices
     int32_t obits_begin, obits_end;
+    int32_t scale_rec;            // record entry (f, 1), f the factor that the stage's sheared ops leave out
+                                  // (-1: it has none); every amplitude takes it at the stage's end
     int32_t sop_begin, sop_end;   // whole-state programs: the stage's StateOps (absolute)
 };
 
@@ -155,9 +158,13 @@ enum PrepKind : int32_t { PR_REG = 0, PR_THREAD = 1, PR_OUTER = 2, PR_BASIS = 3 
 // thread-id bit, so its per-thread factor is the same for every thread of a block.
 // OPF_POSTW: the folded output block has no phase conditioned on a register bit (one factor
 // for all the registers of a thread).
+// OPF_SHEAR: the op's matrix is a real reflection alpha (1, t; t, -1) in every slot, and the kernel
+// applies it as y0 = x0 + t x1, y1 = t x0 - x1; the stage's scale collects the factors alpha.  t is the
+// imaginary part of record entry 0.  Set for all one-qubit ops of a pass or for none.  A (slot, stage)
+// whose factors' product is too small has scale (1, 0), and applies the matrices themselves.
 enum OpFlags : int32_t {
     OPF_REAL = 1, OPF_CHAIN = 2, OPF_UPHASE = 4, OPF_PREW = 8, OPF_PRE_UNI = 16, OPF_POST_UNI = 32,
-    OPF_POSTW = 64
+    OPF_POSTW = 64, OPF_SHEAR = 128
 };
 
 struct OpDesc {
@@ -358,6 +365,7 @@ hipError_t launch_pass_jobs(qs_dtype dt, int n, int S, const PassDesc *pass_host
 size_t fused_lds_bytes(qs_dtype dt, int K);
 // Record entries per stage that fit next to a tile of 2^K amplitudes (two tiles per CU).
 int stage_rec_cap(qs_dtype dt, int K);
+int stage_rec_area(qs_dtype dt, int K);
 
 // Fixed rank: Gram of the 2r half-columns; partial blocks then a fixed-order final sum.
 size_t fr_gram_partials_doubles(int n, int r);

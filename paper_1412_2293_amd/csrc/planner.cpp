@@ -453,12 +453,31 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
         pd.lclassical = 0;
         for (int j = 0; j < K; ++j)
             if (!((touched >> Q[j]) & 1ull)) pd.lclassical |= 1u << j;
+        const uint64_t touched_before = touched;
         for (int q : pb.targets) touched |= 1ull << q;
         uint32_t lcls = pd.lclassical;   // tile-local bits untouched so far in this pass
         const uint32_t kmask = (1u << K) - 1u;
         // register layout the rounds are padded towards (the top tile-local bits)
         const uint32_t top_mask = ((1u << RB) - 1u) << (K - RB);
         const uint32_t load_mask = top_mask;
+
+        // A pass of plain reflections (Hadamard layers with rotation noise) runs sheared: every
+        // one-qubit op a real symmetric reflection about an axis with |m00| >= |m01| (so the factor
+        // m00 it leaves out is small only for noise rotations near a right angle), no folded phase,
+        // no two-qubit op, every target touched before (20-qubit Grover, complex<float>: the two passes of
+        // an iteration 14 % faster than with the matrices' four operations per pair and component).
+        bool shear = !mfma && !state;
+        for (int i : ops_idx) {
+            const PG &x = pg[i];
+            if (x.kind == QS_G_U2 || x.kind == QS_G_CNOT) shear = false;
+            if (!shear || x.kind != QS_G_U1) continue;
+            const double *m = gates[x.gate].m;
+            const bool refl = std::fabs(m[0] * m[0] + m[2] * m[2] - 1.0) <= 1e-14 && std::fabs(m[2] - m[4]) <= 1e-15 &&
+                              std::fabs(m[0] + m[6]) <= 1e-15 && std::fabs(m[0]) >= std::fabs(m[2]) * (1.0 - 1e-9);
+            if (m[1] != 0.0 || m[3] != 0.0 || m[5] != 0.0 || m[7] != 0.0 || !refl || chain_role[x.gate] ||
+                !pre_att[i].empty() || !post_att[i].empty() || !((touched_before >> x.a) & 1ull))
+                shear = false;
+        }
 
         // greedy register rounds, closed also when the current stage reaches its bounds
         auto fill = [&](uint32_t need) {
@@ -481,7 +500,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                     int no = 0;
                     for (auto &at : att)
                         if (local_of[at.cond] < 0) ++no;
-                    rec_c += kPhaseTable + no;
+                    rec_c += kPhaseTable - 2 + no;   // (without the factors of thread-id bit 9)
                     if (no) {
                         ++jobs_c;
                         obits_c += no;
@@ -507,7 +526,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
             RB_ &cur = rounds.back();
             uint32_t cur_mask = cur.forced ? cur.forced : fill(cur.need);
             bool fits_reg = cur.forced ? ((need & ~cur.forced) == 0) : (__builtin_popcount(cur.need | need) <= RB);
-            bool fits_stage = st_ops + 1 <= kStageOps && st_rec + rc <= rec_cap &&
+            bool fits_stage = st_ops + 1 <= kStageOps && st_rec + rc + (shear ? 1 : 0) <= rec_cap &&
                               st_jobs + jc <= kStageJobs && st_obits + oc <= kStageObits;
             if (!cur.ops.empty() && (!fits_reg || !fits_stage)) {
                 RB_ nr;
@@ -565,6 +584,13 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
         pd.op_begin = (int)P.ops.size();
         pd.job_begin = (int)P.jobs.size();
         int rec = 0;
+        // a stage with sheared ops ends with the record entry of their factors' product
+        auto close_scale = [&](StageDesc &sd, int &at) {
+            sd.scale_rec = -1;
+            for (int oi = sd.op_begin; oi < sd.op_end; ++oi)
+                if (P.ops[oi].flags & OPF_SHEAR) sd.scale_rec = at;
+            if (sd.scale_rec >= 0) ++at;
+        };
         for (auto &rd : rounds) {
             uint32_t m = rd.forced;
             if (rd.stage_start) {
@@ -572,6 +598,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                     StageDesc &prev = P.stages.back();
                     prev.round_end = (int)P.rounds.size();
                     prev.op_end = (int)P.ops.size();
+                    close_scale(prev, rec);
                     prev.rec_end = rec;
                     prev.job_end = (int)P.jobs.size();
                     prev.obits_end = (int)P.obits.size();
@@ -616,6 +643,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                         for (int k = 1; k < 8; k += 2)
                             if (gates[x.gate].m[k] != 0.0) real = false;
                         if (real) op.flags |= OPF_REAL;
+                        if (shear) op.flags |= OPF_SHEAR;
                     }
                     rec += 4;
                     if (chain_role[x.gate] == 1) {
@@ -781,6 +809,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
             StageDesc &last = P.stages.back();
             last.round_end = (int)P.rounds.size();
             last.op_end = (int)P.ops.size();
+            close_scale(last, rec);
             last.rec_end = rec;
             last.job_end = (int)P.jobs.size();
             last.obits_end = (int)P.obits.size();
@@ -926,6 +955,9 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                     pd.state = 1;
             }
         }
+        pd.shear = shear && pd.zin_ops == 4 ? 1 : 0;
+        if (!pd.shear)
+            for (int oi = pd.op_begin; oi < (int)P.ops.size(); ++oi) P.ops[oi].flags &= ~OPF_SHEAR;
         if (pd.zin_ops == 3 && K >= 10 && K <= 12 && Q[0] == 0) {
             int high = 0;
             for (int oi = pd.op_begin; oi < (int)P.ops.size(); ++oi) {
