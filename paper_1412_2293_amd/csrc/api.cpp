@@ -460,8 +460,7 @@ qs_status qs_fidelity(qs_state a, int ta, qs_state b, int tb, double *f, double 
     const char *pa = (const char *)a->buf + sb * ta;
     const char *pb = (const char *)b->buf + sb * tb;
     if (a->st != b->st) QS_HIP(hipStreamSynchronize(b->st));
-    QS_HIP(launch_overlaps(pa, 0, pb, a->dt, n, 1, -1, part, out, a->st));
-    QS_HIP(launch_overlaps(pa, 0, pa, a->dt, n, 1, -1, part, out + 5, a->st));
+    QS_HIP(launch_fidelity(pa, pb, a->dt, n, part, out, a->st));
     double h[10];
     QS_HIP(hipMemcpyAsync(h, out, sizeof h, hipMemcpyDeviceToHost, a->st));
     QS_HIP(hipStreamSynchronize(a->st));

@@ -291,6 +291,10 @@ hipError_t launch_overlaps(const void *ref_psi, int ref_slot, const void *psi, q
                            int S, int64_t marked, double *partials, double *out, hipStream_t st,
                            const RunParams *dyn = nullptr);
 // <psi|rho|psi> and Tr rho over vec(rho) of n qubits: out = (Re f, Im f, Re tr, Im tr).
+// out[0..4] and out[5..9] as launch_overlaps gives them for (a, b) and (a, a), one slot each, from one
+// pass over both states (out[6] = 0); partials: 6 << red_log_blocks doubles.
+hipError_t launch_fidelity(const void *a, const void *b, qs_dtype dt, int n, double *partials, double *out,
+                           hipStream_t st);
 hipError_t launch_dm_expect(const void *rho, const void *psi, qs_dtype dt, int n,
                             double *partials, double *out, hipStream_t st);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t st);

@@ -652,11 +652,17 @@ static inline int red_log_blocks(int n)
     return lb;
 }
 
-template <typename R>
+// Bound by the reads: a thread has the vectors of kRedAhead steps in flight and adds them in step
+// order.  REFN: also the reference's own squared norm, written as slot S's partials (x, 0, x); S is 1
+// (two states of 2^27 complex<float>: 380 us, where overlap and norm by themselves took 425 and 301).
+constexpr int kRedAhead = 4;
+
+template <typename R, bool REFN>
 __global__ void __launch_bounds__(kRedThreads) k_overlap_partial(const R *ref, const R *psi, int n,
                                                                  int log_blocks, double *partials)
 {
-    __shared__ double sh[3 * kRedThreads];
+    constexpr int NV = REFN ? 4 : 3;
+    __shared__ double sh[NV * kRedThreads];
     // chunk-major order: the blocks of every slot for one chunk run together, so the
     // reference chunk is read from HBM once and from the caches by the other slots
     const int S = (int)(gridDim.x >> log_blocks);
@@ -667,34 +673,49 @@ __global__ void __launch_bounds__(kRedThreads) k_overlap_partial(const R *ref, c
     double v[4] = {0, 0, 0, 0};
     constexpr int VEC = kVec<R>;
     const uint64_t begin = blk * per;
-    if (per >= (uint64_t)VEC * kRedThreads) {
-        for (uint64_t i = begin + (uint64_t)threadIdx.x * VEC; i < begin + per; i += (uint64_t)VEC * kRedThreads) {
+    auto add = [&](const cx<R> &a, const cx<R> &b) {
+        const double ar = a.re, ai = a.im, br = b.re, bi = b.im;
+        v[0] += ar * br + ai * bi;
+        v[1] += ar * bi - ai * br;
+        v[2] += br * br + bi * bi;
+        if constexpr (REFN) v[3] += ar * ar + ai * ai;
+    };
+    constexpr uint64_t step = (uint64_t)VEC * kRedThreads;
+    if (per >= kRedAhead * step) {
+        for (uint64_t i = begin + (uint64_t)threadIdx.x * VEC; i < begin + per; i += kRedAhead * step) {
+            cx<R> a[kRedAhead][VEC], b[kRedAhead][VEC];
+#pragma unroll
+            for (int u = 0; u < kRedAhead; ++u) {
+                vload(ref, i + u * step, a[u]);
+                vload_nt(p, i + u * step, b[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kRedAhead; ++u)
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) add(a[u][k], b[u][k]);
+        }
+    } else if (per >= step) {
+        for (uint64_t i = begin + (uint64_t)threadIdx.x * VEC; i < begin + per; i += step) {
             cx<R> a[VEC], b[VEC];
             vload(ref, i, a);
             vload_nt(p, i, b);
 #pragma unroll
-            for (int k = 0; k < VEC; ++k) {
-                double ar = a[k].re, ai = a[k].im, br = b[k].re, bi = b[k].im;
-                v[0] += ar * br + ai * bi;
-                v[1] += ar * bi - ai * br;
-                v[2] += br * br + bi * bi;
-            }
+            for (int k = 0; k < VEC; ++k) add(a[k], b[k]);
         }
     } else {
-        for (uint64_t i = begin + threadIdx.x; i < begin + per; i += kRedThreads) {
-            cx<R> a = sload(ref, i), b = sload(p, i);
-            double ar = a.re, ai = a.im, br = b.re, bi = b.im;
-            v[0] += ar * br + ai * bi;
-            v[1] += ar * bi - ai * br;
-            v[2] += br * br + bi * bi;
-        }
+        for (uint64_t i = begin + threadIdx.x; i < begin + per; i += kRedThreads) add(sload(ref, i), sload(p, i));
     }
-    block_sum(sh, v, 3);
+    block_sum(sh, v, NV);
     if (threadIdx.x == 0) {
         double *o = partials + ((uint64_t)slot << log_blocks | blk) * 3;
         o[0] = v[0];
         o[1] = v[1];
         o[2] = v[2];
+        if constexpr (REFN) {
+            o += 3ull << log_blocks;
+            o[0] = o[2] = v[3];
+            o[1] = 0.0;
+        }
     }
 }
 
@@ -767,6 +788,55 @@ __global__ void __launch_bounds__(kRedThreads) k_dm_expect_partial(const R *rho,
             v[2] += rr;
             v[3] += ri;
         }
+    }
+    block_sum(sh, v, 4);
+    if (threadIdx.x == 0)
+        for (int k = 0; k < 4; ++k) partials[(uint64_t)blockIdx.x * 4 + k] = v[k];
+}
+
+// The same where a row is at least one step of the workgroup: a thread keeps its columns and walks
+// the rows of its block, U of them in flight, so that psi_j is read once, conj(psi_i) is uniform over
+// the workgroup, and an element costs one complex multiply-add.  Bound by the reads (2^24 elements of
+// complex<float>: 73 us one element at a time, 27 now; 2^26 of complex<double>: 306 and 204).
+// Grid: (column chunks) x (row chunks), 2^log_blocks in all.
+template <typename R, int U>
+__global__ void __launch_bounds__(kRedThreads) k_dm_expect_rows(const R *rho, const R *psi, int n, int log_blocks,
+                                                                double *partials)
+{
+    __shared__ double sh[4 * kRedThreads];
+    constexpr int VEC = kVec<R>;
+    const int log_cols = n - (VEC == 2 ? 9 : 8);              // column chunks of VEC * kRedThreads
+    const uint64_t rows = 1ull << (n + log_cols - log_blocks);
+    const uint64_t j0 = (blockIdx.x & ((1u << log_cols) - 1u)) * (uint64_t)(VEC * kRedThreads) + threadIdx.x * VEC;
+    const uint64_t i0 = (uint64_t)(blockIdx.x >> log_cols) * rows;
+    double wr[VEC] = {}, wi[VEC] = {};
+    double v[4] = {0, 0, 0, 0};
+    for (uint64_t i = i0; i < i0 + rows; i += U) {
+        cx<R> x[U][VEC], pi[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) vload(rho, ((i + u) << n) + j0, x[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) pi[u] = sload(psi, i + u);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) {
+                const double rr = x[u][k].re, ri = x[u][k].im, pr = pi[u].re, pq = pi[u].im;
+                wr[k] += pr * rr + pq * ri;
+                wi[k] += pr * ri - pq * rr;
+            }
+    }
+    const bool diagonal = j0 >= i0 && j0 < i0 + rows;         // (rows is a multiple of VEC)
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) {
+        if (diagonal) {
+            const cx<R> d = sload(rho, ((j0 + k) << n) + j0 + k);
+            v[2] += (double)d.re;
+            v[3] += (double)d.im;
+        }
+        const cx<R> pj = sload(psi, j0 + k);
+        v[0] += wr[k] * (double)pj.re - wi[k] * (double)pj.im;
+        v[1] += wr[k] * (double)pj.im + wi[k] * (double)pj.re;
     }
     block_sum(sh, v, 4);
     if (threadIdx.x == 0)
@@ -1098,13 +1168,13 @@ hipError_t launch_overlaps(const void *ref_psi, int ref_slot, const void *psi, q
     TimedLaunch tl("reduce", (double)((uint64_t)(S + 1) << n) * amp_bytes(dt), st);
     if (dt == QS_C64) {
         const float *ref = (const float *)ref_psi + ((uint64_t)ref_slot << (n + 1));
-        hipLaunchKernelGGL(k_overlap_partial<float>, dim3(nblk), dim3(kRedThreads), 0, st, ref,
+        hipLaunchKernelGGL((k_overlap_partial<float, false>), dim3(nblk), dim3(kRedThreads), 0, st, ref,
                            (const float *)psi, n, lb, partials);
         hipLaunchKernelGGL(k_overlap_final<float>, dim3(S), dim3(kFinalThreads), 0, st,
                            (const float *)psi, n, lb, marked, partials, out, dyn);
     } else {
         const double *ref = (const double *)ref_psi + ((uint64_t)ref_slot << (n + 1));
-        hipLaunchKernelGGL(k_overlap_partial<double>, dim3(nblk), dim3(kRedThreads), 0, st, ref,
+        hipLaunchKernelGGL((k_overlap_partial<double, false>), dim3(nblk), dim3(kRedThreads), 0, st, ref,
                            (const double *)psi, n, lb, partials);
         hipLaunchKernelGGL(k_overlap_final<double>, dim3(S), dim3(kFinalThreads), 0, st,
                            (const double *)psi, n, lb, marked, partials, out, dyn);
@@ -1112,17 +1182,46 @@ hipError_t launch_overlaps(const void *ref_psi, int ref_slot, const void *psi, q
     return hipGetLastError();
 }
 
+hipError_t launch_fidelity(const void *a, const void *b, qs_dtype dt, int n, double *partials, double *out,
+                           hipStream_t st)
+{
+    const int lb = red_log_blocks(n);
+    TimedLaunch tl("reduce", (double)(2ull << n) * amp_bytes(dt), st);
+    if (dt == QS_C64) {
+        hipLaunchKernelGGL((k_overlap_partial<float, true>), dim3(1u << lb), dim3(kRedThreads), 0, st, (const float *)a,
+                           (const float *)b, n, lb, partials);
+        hipLaunchKernelGGL(k_overlap_final<float>, dim3(2), dim3(kFinalThreads), 0, st, (const float *)b, n, lb, -1,
+                           partials, out, (const RunParams *)nullptr);
+    } else {
+        hipLaunchKernelGGL((k_overlap_partial<double, true>), dim3(1u << lb), dim3(kRedThreads), 0, st,
+                           (const double *)a, (const double *)b, n, lb, partials);
+        hipLaunchKernelGGL(k_overlap_final<double>, dim3(2), dim3(kFinalThreads), 0, st, (const double *)b, n, lb, -1,
+                           partials, out, (const RunParams *)nullptr);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_dm_expect(const void *rho, const void *psi, qs_dtype dt, int n,
                             double *partials, double *out, hipStream_t st)
 {
-    int lb = red_log_blocks(2 * n);
+    const int lb = red_log_blocks(2 * n);
     TimedLaunch tl("reduce", (double)((uint64_t)1 << (2 * n)) * amp_bytes(dt), st);
-    if (dt == QS_C64)
-        hipLaunchKernelGGL(k_dm_expect_partial<float>, dim3(1u << lb), dim3(kRedThreads), 0, st,
-                           (const float *)rho, (const float *)psi, n, lb, partials);
-    else
-        hipLaunchKernelGGL(k_dm_expect_partial<double>, dim3(1u << lb), dim3(kRedThreads), 0, st,
-                           (const double *)rho, (const double *)psi, n, lb, partials);
+    // rows of at least one step (2^9 complex<float>, 2^8 complex<double>), as many column chunks as blocks at most; the
+    // blocks then have at least four rows
+    const int log_cols = n - (dt == QS_C64 ? 9 : 8);
+    const bool by_rows = log_cols >= 0 && log_cols <= lb;
+    const int log_rows = n + log_cols - lb;
+#define QS_DM_EXPECT(KERNEL, R)                                                                                        \
+    hipLaunchKernelGGL(KERNEL, dim3(1u << lb), dim3(kRedThreads), 0, st, (const R *)rho, (const R *)psi, n, lb, partials)
+    if (dt == QS_C64) {
+        if (!by_rows) QS_DM_EXPECT(k_dm_expect_partial<float>, float);
+        else if (log_rows >= 3) QS_DM_EXPECT((k_dm_expect_rows<float, 8>), float);
+        else QS_DM_EXPECT((k_dm_expect_rows<float, 4>), float);
+    } else {
+        if (!by_rows) QS_DM_EXPECT(k_dm_expect_partial<double>, double);
+        else QS_DM_EXPECT((k_dm_expect_rows<double, 8>), double);
+    }
+#undef QS_DM_EXPECT
     hipLaunchKernelGGL(k_sum4_final, dim3(1), dim3(kRedThreads), 0, st, partials, 1 << lb, out);
     return hipGetLastError();
 }

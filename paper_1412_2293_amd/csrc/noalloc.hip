@@ -17,10 +17,10 @@
 namespace qs {
 
 // Partial sums of two overlap reductions of one slot each (red_log_blocks caps the blocks per
-// slot at 2^9, three doubles each, and the density-matrix form at four), then the two 5-double
-// outputs of the final sums.
+// slot at 2^9, three doubles each, and the density-matrix form at four: kNoAllocPartials holds one
+// slot's), then the two 5-double outputs of the final sums.
 constexpr size_t kNoAllocPartials = 2048;
-constexpr size_t kNoAllocDoubles = kNoAllocPartials + 16;
+constexpr size_t kNoAllocDoubles = 2 * kNoAllocPartials + 16;
 static __device__ __align__(256) double scratch[kNoAllocDoubles];
 
 constexpr int kNoAllocMaxDevices = 64;
@@ -79,10 +79,9 @@ extern "C" qs_status qs_fidelity_noalloc(const void *a_dev, const void *b_dev, i
     hipError_t e = noalloc_scratch(&sc);
     if (e != hipSuccess) return hip_fail(e, "fidelity_noalloc: scratch address");
     hipStream_t st = (hipStream_t)hip_stream;
-    double *red = sc + kNoAllocPartials;
-    // the same reductions, in the same order, as qs_fidelity: <a|b> with b's norm, then <a|a>
-    QS_HIP(launch_overlaps(a_dev, 0, b_dev, dt, n_qubits, 1, -1, sc, red, st));
-    QS_HIP(launch_overlaps(a_dev, 0, a_dev, dt, n_qubits, 1, -1, sc, red + 5, st));
+    double *red = sc + 2 * kNoAllocPartials;
+    // the same reductions as qs_fidelity
+    QS_HIP(launch_fidelity(a_dev, b_dev, dt, n_qubits, sc, red, st));
     hipLaunchKernelGGL(k_noalloc_pack, dim3(1), dim3(64), 0, st, red, out_dev);
     QS_HIP(hipGetLastError());
     return QS_OK;

@@ -148,8 +148,8 @@ __device__ __forceinline__ void apply_u1_real(tv<R> (&a)[1 << RB], const cxf<R> 
 }
 
 // The update of a sheared reflection (OPF_SHEAR), up to its factor alpha: two multiply-adds per pair
-// and component, each rounded once, instead of four operations (Grover n = 20, complex<float>, 50
-// slots, 20 iterations: 7.65 ms for the run, 8.90 with the matrices; the passes are bound by issue).
+// and component, each rounded once, instead of four operations (Grover n = 20, complex<float>, 64
+// trajectories, 16 iterations: 7.65 ms a run, 9.37 with the matrices; the passes are bound by issue).
 template <typename R, int RB, int P>
 __device__ __forceinline__ void apply_u1_shear(tv<R> (&a)[1 << RB], R t)
 {
