@@ -295,6 +295,10 @@ hipError_t launch_overlaps(const void *ref_psi, int ref_slot, const void *psi, q
 // pass over both states (out[6] = 0); partials: 6 << red_log_blocks doubles.
 hipError_t launch_fidelity(const void *a, const void *b, qs_dtype dt, int n, double *partials, double *out,
                            hipStream_t st);
+// A density matrix of n qubits: rho_ij times f where only i has both qubits set, conj(f) where only j
+// has; and the CNOT of both sides.
+hipError_t launch_dm_cp(void *rho, qs_dtype dt, int n, int q0, int q1, double fre, double fim, hipStream_t st);
+hipError_t launch_dm_cnot(void *rho, qs_dtype dt, int n, int control, int target, hipStream_t st);
 hipError_t launch_dm_expect(const void *rho, const void *psi, qs_dtype dt, int n,
                             double *partials, double *out, hipStream_t st);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t st);

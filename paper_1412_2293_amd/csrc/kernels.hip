@@ -623,6 +623,57 @@ __global__ void k_scale_pattern(R *psi, int n, uint64_t mask, uint64_t value, in
   }
 }
 
+// A controlled phase or a CNOT on both sides of vec(rho) in one sweep, over the index bits b[0], b[1]
+// (columns) and b[2], b[3] (rows).  A thread takes one of the six parts of a group of 16 entries
+// (uniform over the block but for small matrices), so only what changes is touched:
+//   CP: the six entries with exactly one of row and column selected, times f or conj(f) (with both
+//       selected the phases cancel: f conj(f) over the averaged phase's exp(-e^2) is 1);
+//   CNOT: the six pairs that swap (control b[0] / b[2]).
+// Three sweeps of the averaged phase over quarters, with the index built bit by bit, took 29 us per
+// gate (11 qubits, complex<double>) and this takes 11; two sweeps of a CNOT 26 and 19.
+struct Bits4 {
+    int b[4];        // the four index bits, local bit k -> index bit b[k]
+    int sorted[4];   // the same, ascending (for inserting the zero bits)
+};
+
+template <typename R, bool CNOT>
+__global__ void __launch_bounds__(256) k_dm_pair(R *psi, Bits4 bits, int log_groups, uint64_t total, double fre, double fim)
+{
+    for (uint64_t it = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; it < total;
+         it += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t part = (uint32_t)(it >> log_groups);
+        uint64_t base = it & ((1ull << log_groups) - 1ull);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) base = ins0(base, bits.sorted[k]);
+        auto at = [&](uint32_t l) {
+            uint64_t i = base;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if ((l >> k) & 1u) i |= 1ull << bits.b[k];
+            return i;
+        };
+        const uint32_t o = part % 3u;
+        if constexpr (CNOT) {
+            // side 0, 1: the other side's control is 0 and its target (part / 3) keeps its value;
+            // o = 2: both controls are 1 and both targets flip, column target 0 or 1
+            const uint32_t t = part / 3u;
+            const uint32_t a = o == 0 ? 0x1u | t << 3 : o == 1 ? 0x4u | t << 1 : 0x5u | t << 1;
+            const uint32_t flip = o == 0 ? 0x2u : o == 1 ? 0x8u : 0xAu;
+            const uint64_t i = at(a), k = at(a ^ flip);
+            const cx<R> x = sload(psi, i), y = sload(psi, k);
+            sstore(psi, i, y);
+            sstore(psi, k, x);
+        } else {
+            const bool row = part >= 3u;
+            const uint32_t l = row ? 0xCu | o : 0x3u | o << 2;
+            const uint64_t i = at(l);
+            const cx<R> x = sload(psi, i);
+            const R cr = (R)fre, ci = row ? (R)fim : -(R)fim;
+            sstore(psi, i, cx<R>{cr * x.re - ci * x.im, cr * x.im + ci * x.re});
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------------------
 // FP64 reductions.  Stage 1: each block sums a fixed contiguous range in a fixed order
 // (thread-strided, then an LDS tree); stage 2: one block per slot sums the block partials in
@@ -1015,11 +1066,6 @@ hipError_t launch_sweep_perm(void *psi, qs_dtype dt, int n, int S, int kind, int
 // l = sum_k bit(k of l) << bits[k] are replaced by M times them.  M is 256 complex FP64 values
 // in device memory, row-major, read with uniform loads.
 // ---------------------------------------------------------------------------------------
-struct Bits4 {
-    int b[4];        // the four index bits, local bit k -> index bit b[k]
-    int sorted[4];   // the same, ascending (for inserting the zero bits)
-};
-
 template <typename R>
 __global__ void __launch_bounds__(256) k_4q(R *psi, Bits4 bits, const double *__restrict__ m, uint64_t total)
 {
@@ -1052,6 +1098,118 @@ __global__ void __launch_bounds__(256) k_4q(R *psi, Bits4 bits, const double *__
     }
 }
 
+// The same on the matrix cores: a wave multiplies the 16 x 16 matrix into 16 groups' columns, four
+// products (one per four local indices) for each of the real parts.  Its operand stays in registers,
+// where k_4q reads it anew for every group, and a lane stores to the addresses it loaded: lane
+// (j, m) = (lane / 16, lane % 16) holds group m's local indices 4 c + j (FP64: the result's row is
+// 4 i + j) or 4 j + c (FP32: 4 j + i).  Two tiles at a time keep eight loads and four chains of
+// products in flight.  Bound by the caches on a matrix that they hold (11 qubits, complex<double>,
+// 67 MB: 49 us per sweep with k_4q, 22 here).
+template <typename R>
+struct Mfma16;
+template <>
+struct Mfma16<double> {
+    typedef double v4 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ int local(int c, int j) { return 4 * c + j; }
+    static __device__ __forceinline__ v4 mac(double a, double b, v4 d)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, d, 0, 0, 0);
+    }
+};
+template <>
+struct Mfma16<float> {
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ int local(int c, int j) { return 4 * j + c; }
+    static __device__ __forceinline__ v4 mac(float a, float b, v4 d)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, d, 0, 0, 0);
+    }
+};
+
+constexpr int k4qTiles = 2;   // tiles of 16 groups per wave and step
+
+template <typename R>
+__global__ void __launch_bounds__(256) k_4q_mfma(R *psi, Bits4 bits, const double *__restrict__ mat, uint64_t steps)
+{
+    using M = Mfma16<R>;
+    const int lane = threadIdx.x & 63, m = lane & 15, j = lane >> 4;
+    R sr[4], si[4];
+    uint64_t off[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int l = M::local(c, j);
+        sr[c] = (R)mat[2 * (16 * m + l)];
+        si[c] = (R)mat[2 * (16 * m + l) + 1];
+        off[c] = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if ((l >> k) & 1) off[c] |= 1ull << bits.b[k];
+    }
+    const uint64_t waves = (uint64_t)gridDim.x * 4;
+    for (uint64_t s = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6); s < steps; s += waves) {
+        uint64_t base[k4qTiles];
+        cx<R> x[k4qTiles][4];
+#pragma unroll
+        for (int u = 0; u < k4qTiles; ++u) {
+            base[u] = (s * k4qTiles + u) * 16 + m;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) base[u] = ins0(base[u], bits.sorted[k]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[u][c] = sload(psi, base[u] | off[c]);
+        }
+        typename M::v4 re[k4qTiles], im[k4qTiles];
+#pragma unroll
+        for (int u = 0; u < k4qTiles; ++u) re[u] = im[u] = typename M::v4{(R)0, (R)0, (R)0, (R)0};
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int u = 0; u < k4qTiles; ++u) {
+                re[u] = M::mac(sr[c], x[u][c].re, re[u]);
+                im[u] = M::mac(sr[c], x[u][c].im, im[u]);
+            }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int u = 0; u < k4qTiles; ++u) {
+                re[u] = M::mac(si[c], -x[u][c].im, re[u]);
+                im[u] = M::mac(si[c], x[u][c].re, im[u]);
+            }
+#pragma unroll
+        for (int u = 0; u < k4qTiles; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sstore(psi, base[u] | off[c], cx<R>{re[u][c], im[u][c]});
+    }
+}
+
+// The two sides' bits: columns q0, q1 and rows q0 + n, q1 + n of a density matrix of n qubits.
+static hipError_t launch_dm_pair(void *psi, qs_dtype dt, int n, int q0, int q1, bool cnot, double fre, double fim,
+                                 hipStream_t st)
+{
+    Bits4 b{{q0, q1, q0 + n, q1 + n}, {std::min(q0, q1), std::max(q0, q1), std::min(q0, q1) + n, std::max(q0, q1) + n}};
+    const int log_groups = 2 * n - 4;
+    const uint64_t total = 6ull << log_groups;
+    TimedLaunch tl("dm_pair", (cnot ? 4.0 : 2.0) * (double)total * amp_bytes(dt), st);
+    const dim3 grid(blocks_for(total, 256)), block(256);
+    if (dt == QS_C64) {
+        if (cnot) hipLaunchKernelGGL((k_dm_pair<float, true>), grid, block, 0, st, (float *)psi, b, log_groups, total, fre, fim);
+        else hipLaunchKernelGGL((k_dm_pair<float, false>), grid, block, 0, st, (float *)psi, b, log_groups, total, fre, fim);
+    } else {
+        if (cnot) hipLaunchKernelGGL((k_dm_pair<double, true>), grid, block, 0, st, (double *)psi, b, log_groups, total, fre, fim);
+        else hipLaunchKernelGGL((k_dm_pair<double, false>), grid, block, 0, st, (double *)psi, b, log_groups, total, fre, fim);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_dm_cp(void *rho, qs_dtype dt, int n, int q0, int q1, double fre, double fim, hipStream_t st)
+{
+    return launch_dm_pair(rho, dt, n, q0, q1, false, fre, fim, st);
+}
+
+hipError_t launch_dm_cnot(void *rho, qs_dtype dt, int n, int control, int target, hipStream_t st)
+{
+    return launch_dm_pair(rho, dt, n, control, target, true, 0.0, 0.0, st);
+}
+
 hipError_t launch_sweep_4q(void *psi, qs_dtype dt, int nbits, const int bits[4], const double *m_dev,
                            hipStream_t st)
 {
@@ -1060,6 +1218,16 @@ hipError_t launch_sweep_4q(void *psi, qs_dtype dt, int nbits, const int bits[4],
     std::sort(b.sorted, b.sorted + 4);
     const uint64_t total = 1ull << (nbits - 4);
     TimedLaunch tl("sweep_4q", 2.0 * (double)(1ull << nbits) * amp_bytes(dt), st);
+    if (total >= 16 * k4qTiles) {
+        // (whole steps; smaller matrices, of at most four qubits, take one thread per group)
+        const uint64_t steps = total / (16 * k4qTiles);
+        const unsigned grid = (unsigned)std::min<uint64_t>((steps + 3) / 4, 1024);
+        if (dt == QS_C64)
+            hipLaunchKernelGGL(k_4q_mfma<float>, dim3(grid), dim3(256), 0, st, (float *)psi, b, m_dev, steps);
+        else
+            hipLaunchKernelGGL(k_4q_mfma<double>, dim3(grid), dim3(256), 0, st, (double *)psi, b, m_dev, steps);
+        return hipGetLastError();
+    }
     if (dt == QS_C64)
         hipLaunchKernelGGL(k_4q<float>, dim3(blocks_for(total, 256)), dim3(256), 0, st, (float *)psi, b, m_dev,
                            total);
