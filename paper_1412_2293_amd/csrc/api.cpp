@@ -561,6 +561,8 @@ namespace {
 struct TrajLayout {
     size_t states, tab, gates, edev, passes, stages, rounds, ops, prefs, jobs, obits, sops, chains, wtab, rec, partials, out,
         dyn, total;
+    int window;              // passes that are prepared together
+    PassAreas areas;
 };
 
 struct Plan {
@@ -794,14 +796,21 @@ TrajLayout traj_layout(int n, qs_dtype dt, int T, int n_gates, const Plan &pl)
     L.obits = take(std::max<size_t>(pl.prog.obits.size(), 1) * sizeof(int32_t));
     L.sops = take(std::max<size_t>(pl.prog.sops.size(), 1) * sizeof(StateOp));
     L.chains = take(std::max<size_t>(pl.prog.chain_gates.size() + pl.prog.chain_off.size(), 1) * sizeof(int32_t));
-    // the tiles' outer index bits (at most 2^(n - K) tiles), then the per (slot, tile, outer job)
-    // phase products of the pass being run
+    // per pass of a window: the tiles' outer index bits (at most 2^(n - K) tiles) and the per (slot,
+    // tile, outer job) phase products; and the records.  Passes are prepared up to 32 at a time (what
+    // a preparation takes for one: 9 us) where their areas stay within 8 MiB, else one at a time.
     {
+        const size_t cxs = 2 * (dt == QS_C64 ? 4 : 8);
         const int tb = pl.fused && n > pl.prog.K ? n - pl.prog.K : 0;
         const size_t entries = ((size_t)S << tb) * (size_t)std::max(pl.prog.max_jobs, 1);
-        L.wtab = take(align256((size_t(1) << tb) * sizeof(uint64_t)) + entries * 2 * (dt == QS_C64 ? 4 : 8));
+        L.areas.otab_bytes = align256((size_t(1) << tb) * sizeof(uint64_t));
+        L.areas.wt_stride = align256(L.areas.otab_bytes + entries * cxs);
+        L.areas.rec_stride = align256((size_t)std::max(pl.prog.max_rec, 1) * S * cxs);
+        const size_t one = L.areas.wt_stride + L.areas.rec_stride, passes = pl.prog.passes.size();
+        L.window = (int)std::max<size_t>(1, std::min<size_t>({32, passes, ((size_t)8 << 20) / one}));
+        L.wtab = take(L.areas.wt_stride * L.window);
+        L.rec = take(L.areas.rec_stride * L.window);
     }
-    L.rec = take((size_t)std::max(pl.prog.max_rec, 1) * S * 2 * (dt == QS_C64 ? 4 : 8));
     {
         // the fused runs' per (slot, tile) overlap partials of their last pass
         size_t d = reduce_partials_doubles(n, S);
@@ -1022,30 +1031,40 @@ static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char
                        (const int32_t *)(B + L.obits), (const StateOp *)(B + L.sops)};
         for (size_t p = 0; p < P.passes.size(); ++p) {
             const int64_t init = p == 0 ? (int64_t)init_index : -1;
-            uint64_t *otab = (uint64_t *)(B + L.wtab);
-            char *wtab = B + L.wtab + align256((size_t(1) << (n > P.K ? n - P.K : 0)) * sizeof(uint64_t));
-            if (P.passes[p].expand)
-                QS_HIP(launch_expand_prep(dt, S, &P.passes[p], (int)p, pdv, tab, B + L.rec, (int64_t)init_index, dyn, st));
-            else
-                QS_HIP(launch_pass_prep(dt, S, &P.passes[p], pdv, tab, gdev, B + L.rec, (int64_t)init_index, dyn, st));
+            const size_t at = p % (size_t)L.window;   // the pass's place in its window
+            char *rec = B + L.rec + at * L.areas.rec_stride;
+            uint64_t *otab = (uint64_t *)(B + L.wtab + at * L.areas.wt_stride);
+            char *wtab = (char *)otab + L.areas.otab_bytes;
+            if (at == 0) {
+                const int count = (int)std::min<size_t>(L.window, P.passes.size() - p);
+                QS_HIP(launch_pass_prep(dt, S, &P.passes[p], count, (int)p, pdv, tab, gdev, rec, L.areas,
+                                        (int64_t)init_index, dyn, st));
+                for (int k = 0; k < count; ++k) {
+                    const PassDesc &pk = P.passes[p + k];
+                    char *rk = rec + k * L.areas.rec_stride;
+                    if (pk.expand)
+                        QS_HIP(launch_expand_prep(dt, S, &pk, (int)p + k, pdv, tab, rk, (int64_t)init_index, dyn, st));
+                    bool blocks = false;
+                    for (int ri = pk.round_begin; ri < pk.round_end; ++ri)
+                        blocks = blocks || P.rounds[ri].block_rec >= 0;
+                    if (blocks) QS_HIP(launch_block_prep(dt, S, &pk, pdv, rk, st));
+                }
+                if (!P.passes[p].state)
+                    QS_HIP(launch_pass_jobs(dt, S, &P.passes[p], count, (int)p, pdv, rec, otab, L.areas, init,
+                                            (int64_t)init_index, dyn, st));
+            }
             if (P.passes[p].state) {
                 // one workgroup per slot holds the state: every slot in one launch, the overlaps
                 // from the stored states
-                QS_HIP(launch_state_pass(psi, dt, n, S, &P.passes[p], (int)p, init, pdv, B + L.rec, st, dyn));
+                QS_HIP(launch_state_pass(psi, dt, n, S, &P.passes[p], (int)p, init, pdv, rec, st, dyn));
                 if (overlaps)
                     QS_HIP(launch_overlaps(psi, 0, psi, dt, n, S, pmarked, (double *)(B + L.partials),
                                            (double *)(B + L.out), st, dyn));
                 return QS_OK;
             }
-            bool blocks = false;
-            for (int ri = P.passes[p].round_begin; ri < P.passes[p].round_end; ++ri)
-                blocks = blocks || P.rounds[ri].block_rec >= 0;
-            if (blocks) QS_HIP(launch_block_prep(dt, S, &P.passes[p], pdv, B + L.rec, st));
-            QS_HIP(launch_pass_jobs(dt, n, S, &P.passes[p], pdv, B + L.rec, init, (int64_t)init_index, dyn,
-                                    wtab, otab, st));
             if (p + 1 < P.passes.size() || !overlaps) {
                 QS_HIP(launch_fused_pass(psi, dt, n, S, &P.passes[p], (int)p, init, (int64_t)init_index, pdv,
-                                         B + L.rec, wtab, otab, st, dyn));
+                                         rec, wtab, otab, st, dyn));
                 continue;
             }
             double *part = (double *)(B + L.partials);
@@ -1057,7 +1076,7 @@ static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char
             const size_t slot_bytes = ((size_t)1 << n) * (dt == QS_C64 ? 8 : 16);
             if (S > 1 && fused_walked_bits(n, &P.passes[p], init) < 8 && slot_bytes <= (64u << 10)) {
                 QS_HIP(launch_fused_pass(psi, dt, n, S, &P.passes[p], (int)p, init, (int64_t)init_index, pdv,
-                                         B + L.rec, wtab, otab, st, dyn));
+                                         rec, wtab, otab, st, dyn));
                 QS_HIP(launch_overlaps(psi, 0, psi, dt, n, S, pmarked, part, (double *)(B + L.out), st, dyn));
                 return QS_OK;
             }
@@ -1068,7 +1087,7 @@ static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char
             for (int k = 0; k < 2; ++k) {
                 const bool others = (k == 0) == ref_last;
                 if (others && S == 1) continue;
-                QS_HIP(launch_fused_pass(psi, dt, n, S, &P.passes[p], (int)p, init, (int64_t)init_index, pdv, B + L.rec,
+                QS_HIP(launch_fused_pass(psi, dt, n, S, &P.passes[p], (int)p, init, (int64_t)init_index, pdv, rec,
                                          wtab, otab, st, dyn, part, others ? 1 : 0, others ? S - 1 : 1));
             }
             QS_HIP(launch_overlap_final(psi, dt, n, S, fused_partial_bits(n, &P.passes[p], init), pmarked, part,

@@ -166,12 +166,24 @@ hipError_t launch_phase_chains(double *tab, int S, const int32_t *chain_gates, c
 // basis values), so a block finds its products at wtab + blockIdx * jobs.
 // Also writes otab[tile]: the tile's tile-number bits of the physical index (the walked bits
 // from the tile number, the others at the basis values), from the threads of slot 0, job 0.
+// blockIdx.y: the pass, pass0 + blockIdx.y of the program, with its own areas (PassAreas).
 template <typename R>
-__global__ void k_pass_jobs(int S, int n_jobs, int tiles_log, uint64_t walk, uint64_t fixed_bits, int rec_size,
-                            const OuterJob *__restrict__ jobs, const int32_t *__restrict__ obits,
-                            const cxf<R> *__restrict__ rec_all, const RunParams *dyn, uint64_t classical,
-                            cxf<R> *__restrict__ wtab, uint64_t *__restrict__ otab)
+__global__ void k_pass_jobs(int S, int pass0, int fill_first, uint64_t basis, const PassDesc *__restrict__ passes,
+                            const OuterJob *__restrict__ all_jobs, const int32_t *__restrict__ obits,
+                            const char *__restrict__ rec_base, const RunParams *dyn, char *__restrict__ wt_base,
+                            PassAreas ar)
 {
+    const PassDesc *pd = passes + pass0 + blockIdx.y;
+    const int n_jobs = pd->job_end - pd->job_begin, rec_size = pd->rec_size;
+    const bool fill = pass0 + (int)blockIdx.y == 0 && fill_first && pd->zero_fill;
+    const uint64_t walk = fill ? pd->outer_mask : (pd->outer_mask & ~pd->classical);
+    const int tiles_log = __builtin_popcountll(walk);
+    const uint64_t classical = fill ? 0 : pd->classical;
+    uint64_t fixed_bits = basis & classical;
+    const OuterJob *__restrict__ jobs = all_jobs + pd->job_begin;
+    const cxf<R> *__restrict__ rec_all = reinterpret_cast<const cxf<R> *>(rec_base + blockIdx.y * ar.rec_stride);
+    uint64_t *__restrict__ otab = reinterpret_cast<uint64_t *>(wt_base + blockIdx.y * ar.wt_stride);
+    cxf<R> *__restrict__ wtab = reinterpret_cast<cxf<R> *>(wt_base + blockIdx.y * ar.wt_stride + ar.otab_bytes);
     // thread order (slot, job, tile): the threads of a wave share the job, so its descriptor,
     // condition bits and factors are uniform loads (n_jobs == 0: one row of threads for otab)
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -204,14 +216,20 @@ __global__ void k_pass_jobs(int S, int n_jobs, int tiles_log, uint64_t walk, uin
 // 2^60 stays far inside the float range, and 48 noise-free Hadamards take 2^24 of it.
 constexpr double kShearMin = 0x1p-60;
 
-// One thread per (slot, op), then one wave per (slot, stage) for the products of the stages'
-// factors alpha (`op_blocks` workgroups come first).
+// One thread per (slot, op), then one wave per (slot, stage) for the products of the stages' factors
+// alpha.  blockIdx.y: the pass, pass0 + blockIdx.y of the program, with its own record area; a launch
+// per pass took 5 us of a chain of loads for 0.2 ms passes (Grover n = 20), the same as one for 32.
 template <typename R>
-__global__ void __launch_bounds__(128) k_pass_prep(int S, int op_begin, int n_ops, int rec_size, ProgramDev prog,
-                                                   const double *tab, const qs_gate *gates, cxf<R> *rec_all,
-                                                   uint64_t basis, const RunParams *dyn, int stage_begin, int n_stages,
-                                                   int op_blocks)
+__global__ void __launch_bounds__(128) k_pass_prep(int S, int pass0, ProgramDev prog, const double *tab,
+                                                   const qs_gate *gates, char *rec_base, uint64_t basis,
+                                                   const RunParams *dyn, PassAreas ar)
 {
+    const PassDesc *pd = prog.passes + pass0 + blockIdx.y;
+    if (pd->expand) return;   // (launch_expand_prep)
+    const int op_begin = pd->op_begin, n_ops = pd->op_end - op_begin, rec_size = pd->rec_size;
+    const int stage_begin = pd->stage_begin, n_stages = pd->stage_end - stage_begin;
+    const int op_blocks = (int)(((int64_t)n_ops * S + 127) / 128);
+    cxf<R> *rec_all = reinterpret_cast<cxf<R> *>(rec_base + blockIdx.y * ar.rec_stride);
     if ((int)blockIdx.x >= op_blocks) {
         const int64_t w = (int64_t)((int)blockIdx.x - op_blocks) * 2 + (threadIdx.x >> 6);
         if (w >= (int64_t)S * n_stages) return;
@@ -326,25 +344,26 @@ size_t fused_lds_bytes(qs_dtype dt, int K)
     return (size_t(1) << K) * (dt == QS_C64 ? 8 : 16);
 }
 
-hipError_t launch_pass_prep(qs_dtype dt, int S, const PassDesc *h, ProgramDev prog,
-                            const double *tab, const qs_gate *gates_dev, void *rec, int64_t basis,
+hipError_t launch_pass_prep(qs_dtype dt, int S, const PassDesc *h, int count, int pass0, ProgramDev prog,
+                            const double *tab, const qs_gate *gates_dev, void *rec, const PassAreas &ar, int64_t basis,
                             const RunParams *dyn, hipStream_t st)
 {
-    const int n_ops = h->op_end - h->op_begin;
-    const uint64_t tot = (uint64_t)n_ops * S;
-    if (tot == 0) return hipSuccess;
-    TimedLaunch tl("prep", (double)S * h->rec_size * (dt == QS_C64 ? 8 : 16), st);
-    const unsigned op_blocks = (unsigned)((tot + 127) / 128);
-    const int n_stages = h->stage_end - h->stage_begin;
-    const unsigned blocks = op_blocks + (unsigned)(((uint64_t)S * n_stages + 1) / 2);
+    uint64_t blocks = 0, entries = 0;
+    for (int p = 0; p < count; ++p) {
+        const uint64_t tot = (uint64_t)(h[p].op_end - h[p].op_begin) * S;
+        if (tot == 0 || h[p].expand) continue;
+        blocks = std::max(blocks, (tot + 127) / 128 + ((uint64_t)S * (h[p].stage_end - h[p].stage_begin) + 1) / 2);
+        entries += (uint64_t)h[p].rec_size;
+    }
+    if (blocks == 0) return hipSuccess;
+    TimedLaunch tl("prep", (double)S * entries * (dt == QS_C64 ? 8 : 16), st);
+    const dim3 grid((unsigned)blocks, (unsigned)count);
     if (dt == QS_C64)
-        hipLaunchKernelGGL(k_pass_prep<float>, dim3(blocks), dim3(128), 0, st, S, h->op_begin, n_ops,
-                           h->rec_size, prog, tab, gates_dev, (cxf<float> *)rec, (uint64_t)basis, dyn, h->stage_begin,
-                           n_stages, (int)op_blocks);
+        hipLaunchKernelGGL(k_pass_prep<float>, grid, dim3(128), 0, st, S, pass0, prog, tab, gates_dev, (char *)rec,
+                           (uint64_t)basis, dyn, ar);
     else
-        hipLaunchKernelGGL(k_pass_prep<double>, dim3(blocks), dim3(128), 0, st, S, h->op_begin, n_ops,
-                           h->rec_size, prog, tab, gates_dev, (cxf<double> *)rec, (uint64_t)basis, dyn, h->stage_begin,
-                           n_stages, (int)op_blocks);
+        hipLaunchKernelGGL(k_pass_prep<double>, grid, dim3(128), 0, st, S, pass0, prog, tab, gates_dev, (char *)rec,
+                           (uint64_t)basis, dyn, ar);
     return hipGetLastError();
 }
 
@@ -359,27 +378,27 @@ hipError_t launch_block_prep(qs_dtype dt, int S, const PassDesc *h, ProgramDev p
     return hipGetLastError();
 }
 
-hipError_t launch_pass_jobs(qs_dtype dt, int n, int S, const PassDesc *h, ProgramDev prog, const void *rec,
-                            int64_t init, int64_t basis, const RunParams *dyn, void *wtab, uint64_t *otab,
-                            hipStream_t st)
+hipError_t launch_pass_jobs(qs_dtype dt, int S, const PassDesc *h, int count, int pass0, ProgramDev prog,
+                            const void *rec, void *wt, const PassAreas &ar, int64_t init, int64_t basis,
+                            const RunParams *dyn, hipStream_t st)
 {
-    const int n_jobs = h->job_end - h->job_begin;
-    const bool fill = init >= 0 && h->zero_fill;
-    const uint64_t walk = fill ? h->outer_mask : (h->outer_mask & ~h->classical);
-    const int tiles_log = __builtin_popcountll(walk);
-    const uint64_t classical = fill ? 0 : h->classical;
-    const uint64_t fixed_bits = (uint64_t)basis & classical;
-    const int64_t tot = ((int64_t)S << tiles_log) * (n_jobs > 0 ? n_jobs : 1);
-    TimedLaunch tl("jobs", (double)((int64_t)S << tiles_log) * n_jobs * (dt == QS_C64 ? 8 : 16), st);
-    const unsigned blocks = (unsigned)((tot + 255) / 256);
+    uint64_t blocks = 0, products = 0;
+    for (int p = 0; p < count; ++p) {
+        const int n_jobs = h[p].job_end - h[p].job_begin;
+        const bool fill = pass0 + p == 0 && init >= 0 && h[p].zero_fill;
+        const uint64_t tiles = (uint64_t)S
+                               << __builtin_popcountll(fill ? h[p].outer_mask : h[p].outer_mask & ~h[p].classical);
+        blocks = std::max(blocks, (tiles * (n_jobs > 0 ? n_jobs : 1) + 255) / 256);
+        products += tiles * n_jobs;
+    }
+    TimedLaunch tl("jobs", (double)products * (dt == QS_C64 ? 8 : 16), st);
+    const dim3 grid((unsigned)blocks, (unsigned)count);
     if (dt == QS_C64)
-        hipLaunchKernelGGL(k_pass_jobs<float>, dim3(blocks), dim3(256), 0, st, S, n_jobs, tiles_log, walk, fixed_bits,
-                           h->rec_size, prog.jobs + h->job_begin, prog.obits, (const cxf<float> *)rec, dyn,
-                           classical, (cxf<float> *)wtab, otab);
+        hipLaunchKernelGGL(k_pass_jobs<float>, grid, dim3(256), 0, st, S, pass0, init >= 0 ? 1 : 0, (uint64_t)basis,
+                           prog.passes, prog.jobs, prog.obits, (const char *)rec, dyn, (char *)wt, ar);
     else
-        hipLaunchKernelGGL(k_pass_jobs<double>, dim3(blocks), dim3(256), 0, st, S, n_jobs, tiles_log, walk,
-                           fixed_bits, h->rec_size, prog.jobs + h->job_begin, prog.obits, (const cxf<double> *)rec,
-                           dyn, classical, (cxf<double> *)wtab, otab);
+        hipLaunchKernelGGL(k_pass_jobs<double>, grid, dim3(256), 0, st, S, pass0, init >= 0 ? 1 : 0, (uint64_t)basis,
+                           prog.passes, prog.jobs, prog.obits, (const char *)rec, dyn, (char *)wt, ar);
     return hipGetLastError();
 }
 

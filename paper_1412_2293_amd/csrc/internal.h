@@ -318,9 +318,17 @@ struct ProgramDev {
     const StateOp *sops;
 };
 
-// Records of pass `pass_host` for all S slots into rec (S * rec_size complex entries).
-hipError_t launch_pass_prep(qs_dtype dt, int S, const PassDesc *pass_host, ProgramDev prog,
-                            const double *tab, const qs_gate *gates_dev, void *rec, int64_t basis,
+// The areas of the passes that are prepared together: pass k of them has its records (S * rec_size
+// complex entries) at rec + k * rec_stride, and at wt + k * wt_stride its tiles' outer index bits
+// (otab) and, otab_bytes on, its per-tile products (wtab).
+struct PassAreas {
+    uint64_t rec_stride, wt_stride, otab_bytes;
+};
+
+// Records of the passes pass0, ..., pass0 + count - 1 (pass_host: the first one's descriptor) for all S
+// slots, except those marked `expand`.
+hipError_t launch_pass_prep(qs_dtype dt, int S, const PassDesc *pass_host, int count, int pass0, ProgramDev prog,
+                            const double *tab, const qs_gate *gates_dev, void *rec, const PassAreas &ar, int64_t basis,
                             const RunParams *dyn, hipStream_t st);
 // Sets the fused kernels' LDS limit (done by the first launch otherwise); call before capturing
 // a graph.
@@ -364,12 +372,11 @@ int fused_partial_bits(int n, const PassDesc *pass_host, int64_t init);
 // plans only).
 hipError_t launch_block_prep(qs_dtype dt, int S, const PassDesc *pass_host, ProgramDev prog, void *rec,
                              hipStream_t st);
-// The per-tile products of a pass's outer jobs into wtab and the tiles' outer index bits into
-// otab (after launch_pass_prep of the pass); the same init / basis / dyn as the pass's
-// launch_fused_pass.
-hipError_t launch_pass_jobs(qs_dtype dt, int n, int S, const PassDesc *pass_host, ProgramDev prog, const void *rec,
-                            int64_t init, int64_t basis, const RunParams *dyn, void *wtab, uint64_t *otab,
-                            hipStream_t st);
+// The per-tile products of the same passes' outer jobs and the tiles' outer index bits (after the
+// passes' records); init (pass 0's, when it is among them) / basis / dyn as for launch_fused_pass.
+hipError_t launch_pass_jobs(qs_dtype dt, int S, const PassDesc *pass_host, int count, int pass0, ProgramDev prog,
+                            const void *rec, void *wt, const PassAreas &ar, int64_t init, int64_t basis,
+                            const RunParams *dyn, hipStream_t st);
 size_t fused_lds_bytes(qs_dtype dt, int K);
 // Record entries per stage that fit next to a tile of 2^K amplitudes (two tiles per CU).
 int stage_rec_cap(qs_dtype dt, int K);
