@@ -532,6 +532,69 @@ __global__ void __launch_bounds__(256) k_2q(R *psi, int n, int qa, int qb, const
   }
 }
 
+// Dense two-qubit sweep of complex<float> with qubit 0: both its values lie in one 16-byte vector, so a
+// thread's group is the vectors at the other qubit's two values.  m: local index bit(0) + 2 bit(hi).
+__global__ void __launch_bounds__(256) k_2q_low(float *psi, int n, int hi, M32 m32, int log_items, uint64_t total)
+{
+  cx<float> m[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) m[k] = {(float)m32.v[2 * k], (float)m32.v[2 * k + 1]};
+  for (uint64_t it = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; it < total;
+       it += (uint64_t)gridDim.x * blockDim.x) {
+    float *p = psi + ((it >> log_items) << (n + 1));
+    const uint64_t i0 = ins0((it & ((1ull << log_items) - 1)) * 2, hi), i1 = i0 | (1ull << hi);
+    cx<float> a[4];
+    vload_nt(p, i0, a);
+    vload_nt(p, i1, a + 2);
+    cx<float> y[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        y[r] = cfma(m[4 * r + 3], a[3], cfma(m[4 * r + 2], a[2], cfma(m[4 * r + 1], a[1], cmul(m[4 * r], a[0]))));
+    vstore_nt(p, i0, y);
+    vstore_nt(p, i1, y + 2);
+  }
+}
+
+// The same with the other qubit among the lane bits (hi <= 6): every lane loads its own vector, so that
+// a wave's access is one contiguous 1 KiB, and takes the other one from lane l ^ 2^(hi - 1).  Bound by HBM:
+// n = 27, qubits 0 and 1: 417 us with four loads of 8 bytes per thread, 380 with two of 16 to a group's
+// own thread, 347 here.  Vectors per slot are a multiple of 256 U.
+template <int U>
+__global__ void __launch_bounds__(256) k_2q_low_lane(float *psi, int n, int hi, M32 m32, int log_items, uint64_t total)
+{
+  const int lmask = 1 << (hi - 1);
+  cx<float> m[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) m[k] = {(float)m32.v[2 * k], (float)m32.v[2 * k + 1]};
+  const bool b = (threadIdx.x & (unsigned)lmask) != 0;
+  // rows 2 b and 2 b + 1: own columns 2 b, 2 b + 1, then the partner's
+  cx<float> k0[4], k1[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+      k0[c] = b ? m[8 + (c ^ 2)] : m[c];
+      k1[c] = b ? m[12 + (c ^ 2)] : m[4 + c];
+  }
+  for (uint64_t blk = blockIdx.x; blk * (256 * U) < total; blk += gridDim.x) {
+    cx<float> a[U][2];
+    float *at[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t it = blk * (256 * U) + (uint64_t)u * 256 + threadIdx.x;
+        at[u] = psi + ((it >> log_items) << (n + 1)) + 4 * (it & ((1ull << log_items) - 1));
+        vload_nt(at[u], 0, a[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        cx<float> o[2], y[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) o[k] = {__shfl_xor(a[u][k].re, lmask), __shfl_xor(a[u][k].im, lmask)};
+        y[0] = cfma(k0[3], o[1], cfma(k0[2], o[0], cfma(k0[1], a[u][1], cmul(k0[0], a[u][0]))));
+        y[1] = cfma(k1[3], o[1], cfma(k1[2], o[0], cfma(k1[1], a[u][1], cmul(k1[0], a[u][0]))));
+        vstore_nt(at[u], 0, y);
+    }
+  }
+}
+
 // Dense two-qubit sweep with the lower qubit among a wave's lane bits and the upper one above
 // the vectors a wave spans: each lane loads its vector in both halves of the upper qubit (two
 // contiguous 1 KiB accesses per wave), takes the partner lane's two vectors (lane l ^ 2^LB,
@@ -1267,6 +1330,24 @@ hipError_t launch_sweep_2q(void *psi, qs_dtype dt, int n, int S, int qa, int qb,
                            const double *m32, hipStream_t st)
 {
     TimedLaunch tl("sweep_2q", 2.0 * (double)((uint64_t)S << n) * amp_bytes(dt), st);
+    if (dt == QS_C64 && std::min(qa, qb) == 0) {
+        // (the order of the sums is the general form's for qa = 0; for qb = 0 the middle two terms swap)
+        M32 m{};
+        auto sw = [&](int l) { return qa == 0 ? l : ((l & 1) << 1) | (l >> 1); };
+        for (int r = 0; r < 4; ++r)
+            for (int c = 0; c < 4; ++c)
+                for (int k = 0; k < 2; ++k) m.v[2 * (4 * sw(r) + sw(c)) + k] = m32[2 * (4 * r + c) + k];
+        const int hi = std::max(qa, qb);
+        const uint64_t vectors = (uint64_t)S << (n - 1);
+        // (the lane form needs whole workgroups of 512 vectors in a slot)
+        if (hi <= 6 && n - 1 >= 9)
+            hipLaunchKernelGGL(k_2q_low_lane<2>, dim3(blocks_for(vectors, 512)), dim3(256), 0, st, (float *)psi, n, hi, m,
+                               n - 1, vectors);
+        else
+            hipLaunchKernelGGL(k_2q_low, dim3(blocks_for(vectors / 2, 256)), dim3(256), 0, st, (float *)psi, n, hi, m,
+                               n - 2, vectors / 2);
+        return hipGetLastError();
+    }
     if (dt == QS_C64 ? sweep_2q_lane((float *)psi, n, S, qa, qb, m32, st)
                      : sweep_2q_lane((double *)psi, n, S, qa, qb, m32, st))
         return hipGetLastError();
