@@ -1278,6 +1278,7 @@ qs_status qs_plan_describe(const qs_gate *gates, int n_gates, int n, qs_dtype dt
         I("expand", pd.expand);
         I("state", pd.state);
         I("shear", pd.shear);
+        I("defer", pd.defer);
         I("rec_size", pd.rec_size);
         I("load_round", pd.load_round);
         I("load_reg_mask", P.rounds[pd.load_round].reg_mask);

@@ -159,7 +159,7 @@ constexpr int kMinWaves = (sizeof(R) == 4 && RB == 4) ? 4 : 1;
 // every one-qubit op has a real matrix and no folded phase.  ZV 6: as 4, and every one-qubit op is
 // a sheared reflection (Grover's Hadamard layers).  ZV 5:
 // no one-qubit op at all (density-matrix passes of dense two-qubit superoperators and diagonal
-// patterns).
+// patterns).  ZV 7: as 5, with the diagonal ops' products collected.
 // MIX: whether the pass has ops other than one-qubit gates (dense two-qubit gates, diagonal
 // patterns left standalone); without them the op loop holds only the one-qubit paths (QFT
 // and random-layer passes 1-2% faster).
@@ -378,6 +378,66 @@ __global__ void __launch_bounds__((kWideTile<R, RB>) ? 256 : 512)
         }
     };
 
+    // ZV 7 (density matrices: many averaged phases between few superoperators): a diagonal op on one or
+    // two register bits only multiplies its factor into the thread's product for those bits, and the
+    // products reach the registers before the next dense op or exchange.  Applied one by one, each op
+    // passed over half or a quarter of the registers, with a test per register (density matrix of the
+    // 12-qubit QFT, complex<float>, 198 such ops in three passes: 284 us in the passes, 249 with the
+    // products; of the 13-qubit one 1161 and 953 us for the run).
+    constexpr bool DEFER = ZV == 7;
+    cxf<R> dw1[RB], dw2 = {(R)1, (R)0};
+#pragma unroll
+    for (int k = 0; k < RB; ++k) dw1[k] = dw2;
+    uint32_t dirty = 0;          // bit k: dw1[k] holds factors; bit 8: dw2, for the register bits in dpair
+    uint32_t dpair = 0;
+    auto flush = [&]() {
+        if (dirty == 0) return;
+        const cxf<R> one = {(R)1, (R)0};
+        auto single = [&](auto pc) {
+            constexpr int P = decltype(pc)::value;
+            if (P < RB && ((dirty >> P) & 1u)) {
+                phase_on_bit<R, RB, P % RB>(a, dw1[P % RB]);
+                dw1[P % RB] = one;
+            }
+        };
+        single(std::integral_constant<int, 0>{});
+        single(std::integral_constant<int, 1>{});
+        single(std::integral_constant<int, 2>{});
+        single(std::integral_constant<int, 3>{});
+        if (dirty & 256u) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                if (((uint32_t)r & dpair) == dpair) a[r] = tvec(mul(dw2, cx<R>(a[r])));
+            dw2 = one;
+        }
+        dirty = 0;
+    };
+    auto defer = [&](const OpDesc *op) {
+        if ((outer & op->omask) != op->ovalue) return;
+        const int p0 = op->p0, p1 = op->p1;
+        if (p0 < 0) {
+            diag_op(op);
+            return;
+        }
+        const uint32_t rm = prog.rounds[cur_ri].reg_mask;
+        const bool hit = (lthr & op->lmask) == (op->lvalue & ~rm);
+        const cxf<R> f = rec[op->rec];
+        const cxf<R> w = {hit ? f.re : (R)1, hit ? f.im : (R)0};
+        if (p1 >= 0) {
+            const uint32_t pair = 1u << p0 | 1u << p1;
+            if ((dirty & 256u) && pair != dpair) flush();
+            dpair = pair;
+            dirty |= 256u;
+            dw2 = mul(dw2, w);
+            return;
+        }
+        dirty |= 1u << p0;
+        if (p0 == 0) dw1[0] = mul(dw1[0], w);
+        else if (RB > 1 && p0 == 1) dw1[1 % RB] = mul(dw1[1 % RB], w);
+        else if (RB > 2 && p0 == 2) dw1[2 % RB] = mul(dw1[2 % RB], w);
+        else dw1[RB - 1] = mul(dw1[RB - 1], w);
+    };
+
     for (int si = pd->stage_begin; si < pd->stage_end; ++si) {
         const StageDesc sd = prog.stages[si];
         bool sheared = false;   // the stage's one-qubit ops leave out their factors
@@ -545,7 +605,7 @@ __global__ void __launch_bounds__((kWideTile<R, RB>) ? 256 : 512)
                     const bool bit1 = (blocal & prog.rounds[cur_ri].roff[1 << op->p0]) != 0;
                     if (bit1) dispatch_u1_pp<R, RB, 0, 1, 2>(op->p0, true, a, m, pre, post);
                     else dispatch_u1_pp<R, RB, 0, 1, 1>(op->p0, true, a, m, pre, post);
-                } else if (ZV != 5 && type == OP_U1) {
+                } else if (ZV != 5 && ZV != 7 && type == OP_U1) {
                     cxf<R> m[4] = {orec[0], orec[1], orec[2], orec[3]};
                     PhaseSet<R, RB> pre, post;
                     const int flags = op->flags;
@@ -580,14 +640,17 @@ __global__ void __launch_bounds__((kWideTile<R, RB>) ? 256 : 512)
                     dispatch_u1<R, RB>(op->p0, (flags & OPF_REAL) != 0, prekind, zin, postkind, a, m, pre,
                                        post);
                 } else if (MIX && type == OP_U2) {
+                    if constexpr (DEFER) flush();
                     cxf<R> m[16];
 #pragma unroll
                     for (int k = 0; k < 16; ++k) m[k] = orec[k];
                     dispatch_u2<R, RB>(op->p0, op->p1, (op->flags & OPF_REAL) != 0, a, m);
                 } else if (MIX) {
-                    diag_op(op);
+                    if constexpr (DEFER) defer(op);
+                    else diag_op(op);
                 }
             }
+            if constexpr (DEFER) flush();
             }
         }
         if constexpr (ZV == 6)
@@ -748,6 +811,7 @@ static hipError_t fused_attr()
     if (e == hipSuccess) e = fused_attr_mix<R, RB, false, 4>();
     if (e == hipSuccess) e = fused_attr_mix<R, RB, false, 6>();
     if (e == hipSuccess) e = fused_attr_one<R, RB, false, false, 5, true>();
+    if (e == hipSuccess) e = fused_attr_one<R, RB, false, false, (RB == 4 ? 7 : 5), true>();
     if constexpr (kBlockVariant<R, RB>) {
         // block rounds replace the op-by-op loop: no zero-input paths there
         if (e == hipSuccess) e = fused_attr_one<R, RB, false, true, 0, true>();
@@ -796,7 +860,8 @@ static hipError_t launch_t(R *psi, int n, int S, const PassDesc &h, int pass_ind
         if (h.shear) QS_FUSED_LAUNCH(false, 6);
         else QS_FUSED_LAUNCH(false, 4);
     } else if (h.zin_ops == 5) {
-        QS_FUSED_LAUNCH_M(false, false, 5, true);
+        if (RB == 4 && h.defer) QS_FUSED_LAUNCH_M(false, false, (RB == 4 ? 7 : 5), true);
+        else QS_FUSED_LAUNCH_M(false, false, 5, true);
     } else if (h.zin_ops == 2) {
         if (h.uni_kernel) QS_FUSED_LAUNCH(true, 2);
         else QS_FUSED_LAUNCH(false, 2);

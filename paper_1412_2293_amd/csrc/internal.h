@@ -109,6 +109,7 @@ struct PassDesc {
                                   // 3 all, each with a real matrix, no input phase and at most
                                   // a uniform output factor; 4 none, each with a real matrix and
                                   // no folded phase; 5 the pass has no one-qubit op
+    int32_t defer;                // zin_ops 5, and the products of its diagonal ops are collected
     int32_t shear;                // zin_ops 4, and every one-qubit op runs sheared (OPF_SHEAR)
     int32_t mixed_ops;            // the pass has ops other than one-qubit gates
     int32_t expand;               // zin_ops 3 with enough targets: the pass is the product of its
@@ -169,7 +170,9 @@ enum OpFlags : int32_t {
 
 struct OpDesc {
     int32_t type;
-    int32_t p0, p1;               // register-bit positions of the target(s)
+    int32_t p0, p1;               // register-bit positions of the target(s); DIAG: of the condition's
+                                  // bits when one (p0) or two (p0 < p1) are in registers, all set;
+                                  // else -1
     int32_t flags;
     int32_t rec;                  // record offset (complex entries) within the slot's block
     int32_t pre_rec, post_rec;    // phase blocks (-1: none)
