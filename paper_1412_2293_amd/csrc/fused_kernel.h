@@ -382,8 +382,8 @@ __global__ void __launch_bounds__((kWideTile<R, RB>) ? 256 : 512)
     // two register bits only multiplies its factor into the thread's product for those bits, and the
     // products reach the registers before the next dense op or exchange.  Applied one by one, each op
     // passed over half or a quarter of the registers, with a test per register (density matrix of the
-    // 12-qubit QFT, complex<float>, 198 such ops in three passes: 284 us in the passes, 249 with the
-    // products; of the 13-qubit one 1161 and 953 us for the run).
+    // 12-qubit QFT, complex<float>, 198 such ops in three passes: 284 us in the passes, 182 with the
+    // products).
     constexpr bool DEFER = ZV == 7;
     cxf<R> dw1[RB], dw2 = {(R)1, (R)0};
 #pragma unroll
@@ -412,17 +412,8 @@ __global__ void __launch_bounds__((kWideTile<R, RB>) ? 256 : 512)
         }
         dirty = 0;
     };
-    auto defer = [&](const OpDesc *op) {
-        if ((outer & op->omask) != op->ovalue) return;
-        const int p0 = op->p0, p1 = op->p1;
-        if (p0 < 0) {
-            diag_op(op);
-            return;
-        }
-        const uint32_t rm = prog.rounds[cur_ri].reg_mask;
-        const bool hit = (lthr & op->lmask) == (op->lvalue & ~rm);
-        const cxf<R> f = rec[op->rec];
-        const cxf<R> w = {hit ? f.re : (R)1, hit ? f.im : (R)0};
+    // w: the thread's factor on register bit p0, or on p0 and p1
+    auto collect = [&](int p0, int p1, cxf<R> w) {
         if (p1 >= 0) {
             const uint32_t pair = 1u << p0 | 1u << p1;
             if ((dirty & 256u) && pair != dpair) flush();
@@ -436,6 +427,50 @@ __global__ void __launch_bounds__((kWideTile<R, RB>) ? 256 : 512)
         else if (RB > 1 && p0 == 1) dw1[1 % RB] = mul(dw1[1 % RB], w);
         else if (RB > 2 && p0 == 2) dw1[2 % RB] = mul(dw1[2 % RB], w);
         else dw1[RB - 1] = mul(dw1[RB - 1], w);
+    };
+    // The diagonal ops from oi on, up to the next dense op or the round's end: their descriptors and
+    // factors four at a time, so that four ops wait on two scalar loads in turn instead of eight.
+    auto diag_run = [&](int oi, int oe) {
+        const uint32_t rm = prog.rounds[cur_ri].reg_mask;
+        for (;;) {
+            constexpr int B = 4;
+            int type[B], p0[B], p1[B], at[B];
+            uint32_t lm[B], lv[B], cr[B];
+            uint64_t om[B], ov[B];
+#pragma unroll
+            for (int k = 0; k < B; ++k) {
+                const OpDesc *op = prog.ops + (oi + k < oe ? oi + k : oe - 1);
+                type[k] = op->type;
+                p0[k] = op->p0;
+                p1[k] = op->p1;
+                at[k] = op->rec;
+                lm[k] = op->lmask;
+                lv[k] = op->lvalue;
+                cr[k] = op->creg;
+                om[k] = op->omask;
+                ov[k] = op->ovalue;
+            }
+            cxf<R> f[B];
+#pragma unroll
+            for (int k = 0; k < B; ++k) f[k] = rec[at[k]];
+#pragma unroll
+            for (int k = 0; k < B; ++k) {
+                if (oi >= oe || type[k] == OP_U2) return oi;
+                ++oi;
+                if ((outer & om[k]) != ov[k]) continue;
+                const bool hit = (lthr & lm[k]) == (lv[k] & ~rm);
+                const cxf<R> w = {hit ? f[k].re : (R)1, hit ? f[k].im : (R)0};
+                if (p0[k] >= 0) {
+                    collect(p0[k], p1[k], w);
+                } else if (cr[k]) {
+#pragma unroll
+                    for (int r = 0; r < NR; ++r)
+                        if (((uint32_t)r & cr[k]) == cr[k]) a[r] = tvec(mul(w, cx<R>(a[r])));
+                } else {
+                    diag_op(prog.ops + oi - 1);
+                }
+            }
+        }
     };
 
     for (int si = pd->stage_begin; si < pd->stage_end; ++si) {
@@ -575,8 +610,12 @@ __global__ void __launch_bounds__((kWideTile<R, RB>) ? 256 : 512)
             }
             const int oe = rd->op_end;
             for (int oi = rd->op_begin; oi < oe; ++oi) {
+                if constexpr (DEFER) {
+                    oi = diag_run(oi, oe);
+                    if (oi >= oe) break;
+                }
                 const OpDesc *op = prog.ops + oi;
-                const int type = op->type;
+                const int type = DEFER ? (int)OP_U2 : op->type;
                 const cxf<R> *__restrict__ orec = rec + op->rec;
                 if (ZV == 6 && sheared && type == OP_U1) {
                     dispatch_u1_shear<R, RB>(op->p0, a, orec[0].im);
@@ -646,8 +685,7 @@ __global__ void __launch_bounds__((kWideTile<R, RB>) ? 256 : 512)
                     for (int k = 0; k < 16; ++k) m[k] = orec[k];
                     dispatch_u2<R, RB>(op->p0, op->p1, (op->flags & OPF_REAL) != 0, a, m);
                 } else if (MIX) {
-                    if constexpr (DEFER) defer(op);
-                    else diag_op(op);
+                    diag_op(op);
                 }
             }
             if constexpr (DEFER) flush();
@@ -811,7 +849,7 @@ static hipError_t fused_attr()
     if (e == hipSuccess) e = fused_attr_mix<R, RB, false, 4>();
     if (e == hipSuccess) e = fused_attr_mix<R, RB, false, 6>();
     if (e == hipSuccess) e = fused_attr_one<R, RB, false, false, 5, true>();
-    if (e == hipSuccess) e = fused_attr_one<R, RB, false, false, (RB == 4 ? 7 : 5), true>();
+    if (e == hipSuccess) e = fused_attr_one<R, RB, false, false, (RB >= 3 ? 7 : 5), true>();
     if constexpr (kBlockVariant<R, RB>) {
         // block rounds replace the op-by-op loop: no zero-input paths there
         if (e == hipSuccess) e = fused_attr_one<R, RB, false, true, 0, true>();
@@ -860,7 +898,7 @@ static hipError_t launch_t(R *psi, int n, int S, const PassDesc &h, int pass_ind
         if (h.shear) QS_FUSED_LAUNCH(false, 6);
         else QS_FUSED_LAUNCH(false, 4);
     } else if (h.zin_ops == 5) {
-        if (RB == 4 && h.defer) QS_FUSED_LAUNCH_M(false, false, (RB == 4 ? 7 : 5), true);
+        if (RB >= 3 && h.defer) QS_FUSED_LAUNCH_M(false, false, (RB >= 3 ? 7 : 5), true);
         else QS_FUSED_LAUNCH_M(false, false, 5, true);
     } else if (h.zin_ops == 2) {
         if (h.uni_kernel) QS_FUSED_LAUNCH(true, 2);

@@ -184,6 +184,7 @@ struct OpDesc {
     uint32_t lmask, lvalue;       // DIAG: tile-local condition (l & lmask) == lvalue
     // U1: register-index bits whose tile-local qubits no non-diagonal gate has touched before
     // this op (they still hold the run's basis bits, so registers that disagree there are zero)
+    // DIAG: the condition's register-index bits when all are set, else 0
     uint32_t creg;
     uint64_t omask, ovalue;       // DIAG: tile condition (outer index & omask) == ovalue
 };

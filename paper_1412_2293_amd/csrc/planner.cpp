@@ -754,9 +754,12 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                     op.ovalue = value & pd.outer_mask;
                     op.p0 = op.p1 = -1;
                     const uint32_t in_regs = lm & m;
-                    if (__builtin_popcount(in_regs) <= 2 && (lv & m) == in_regs)
-                        for (int j = 0; j < K; ++j)
-                            if ((in_regs >> j) & 1u) (op.p0 < 0 ? op.p0 : op.p1) = reg_index[j];
+                    if ((lv & m) == in_regs)
+                        for (int j = 0; j < K; ++j) {
+                            if (!((in_regs >> j) & 1u)) continue;
+                            op.creg |= 1u << reg_index[j];
+                            if (__builtin_popcount(in_regs) <= 2) (op.p0 < 0 ? op.p0 : op.p1) = reg_index[j];
+                        }
                     rec += 1;
                 }
                 op.pref_end = (int)P.prefs.size();
@@ -918,18 +921,18 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
             }
             // 5: no one-qubit op at all
             if (u1 == 0 && pd.mixed_ops && !pd.blocks) pd.zin_ops = 5;
-            // Its diagonal ops' products are collected in 16-register tiles, where there are at least two
-            // such ops for each dense op and round, which end a collection.  (With 8 registers an op
-            // passes over 2 or 4 of them, and the products' registers cost more: density matrix of the
-            // 12-qubit QFT, complex<double>, 558 us with, 544 without; complex<float>, 16 registers, 438
-            // and 481.  Grover's 13 qubits, one diagonal op per layer, complex<double>: 14.9 ms and 14.4.)
+            // Its diagonal ops' products are collected in tiles of 8 or 16 registers, where there are at
+            // least two such ops for each dense op and round, which end a collection (density matrix of
+            // the QFT, 13 qubits: complex<float>, 16 registers, 1161 us one by one, 800 collected;
+            // complex<double>, 8 registers, 1600 and 1265.  Grover's 13 qubits, one diagonal op per layer,
+            // complex<double>: 14.4 ms and 14.9).
             if (pd.zin_ops == 5) {
                 int collect = 0, ends = pd.round_end - pd.round_begin;
                 for (int oi = pd.op_begin; oi < (int)P.ops.size(); ++oi) {
                     if (P.ops[oi].type == OP_U2) ++ends;
                     else if (P.ops[oi].p0 >= 0) ++collect;
                 }
-                pd.defer = RB == 4 && collect >= 2 * ends ? 1 : 0;
+                pd.defer = RB >= 3 && collect >= 2 * ends ? 1 : 0;
             }
             // rounds that run as one straight-line sequence: in a pass of kind 3, k ops on
             // register bits k-1, ..., 0 in turn; of kind 4, on bits 0, ..., k-1, or two runs on

@@ -1,4 +1,4 @@
-"""GPU: density-matrix passes that collect the products of their diagonal ops (16-register tiles): noisy
+"""GPU: density-matrix passes that collect the products of their diagonal ops (tiles of 8 and 16 registers): noisy
 controlled phases on every pair of qubits between gates that end a collection, patterns on one, two
 (of changing pairs) and more register bits, with clear condition bits among them, against the oracle.
 
@@ -38,6 +38,8 @@ def phases_between(n, seed):
     (phases_between, 5, {"fuse": 1, "tile_bits": 8, "reg_bits": 4, "run_bits": 2}),
     (phases_between, 6, {"fuse": 1, "tile_bits": 9, "reg_bits": 4, "run_bits": 3}),
     (phases_between, 7, {"fuse": 1, "tile_bits": 12, "reg_bits": 4, "run_bits": 4}),
+    (phases_between, 6, {"fuse": 1, "tile_bits": 8, "reg_bits": 3, "run_bits": 2}),
+    (phases_between, 7, {"fuse": 1, "tile_bits": 11, "reg_bits": 3, "run_bits": 3}),
     (lambda n, s: qft(n, seed=s, x=45), 7, {"fuse": 1, "tile_bits": 12, "reg_bits": 4, "run_bits": 4}),
     (lambda n, s: qft(n, seed=s, x=9), 6, {"fuse": 1, "tile_bits": 7, "reg_bits": 4, "run_bits": 2}),
 ])
