@@ -151,11 +151,10 @@ def main():
             valu_busy = tr.get("valu_busy_by_pass")
     # Algorithmic bytes of a pass count the tiles that can hold amplitude and the support
     # amplitudes read inside them (a run starts from a basis state); the pass that dominates
-    # the step is bound by vector-instruction issue, whose profiled busy fraction is given
-    # beside the HBM figures.
+    # the step is bound by its writes; its vector busy fraction is given beside the HBM figures.
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": "k_fused<float,RB>", "launches_per_step": fused["launches"] / a.steps,
+                "kernel": "fused passes (k_expand<float>, k_fused<float,RB>)", "launches_per_step": fused["launches"] / a.steps,
                 "avg_launch_ms": round(launch_ms, 4), "alg_bytes_per_launch": launch_bytes,
                 "valu_busy_by_pass_profiled": valu_busy}
     out = {
