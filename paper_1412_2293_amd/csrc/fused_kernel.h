@@ -849,7 +849,6 @@ static hipError_t fused_attr()
     if (e == hipSuccess) e = fused_attr_mix<R, RB, false, 4>();
     if (e == hipSuccess) e = fused_attr_mix<R, RB, false, 6>();
     if (e == hipSuccess) e = fused_attr_one<R, RB, false, false, 5, true>();
-    if (e == hipSuccess) e = fused_attr_one<R, RB, false, false, (RB >= 3 ? 7 : 5), true>();
     if constexpr (kBlockVariant<R, RB>) {
         // block rounds replace the op-by-op loop: no zero-input paths there
         if (e == hipSuccess) e = fused_attr_one<R, RB, false, true, 0, true>();
@@ -858,13 +857,13 @@ static hipError_t fused_attr()
     return e;
 }
 
-template <typename R, int RB>
+template <typename R, int RB, bool DEF = false>
 static hipError_t launch_t(R *psi, int n, int S, const PassDesc &h, int pass_index, int rec_cap,
                            int64_t init, int64_t basis, const RunParams *dyn, ProgramDev prog, const void *rec,
                            const void *wtab, const uint64_t *otab, size_t lds, hipStream_t st,
                            double *ovl, int slot_base, int slots)
 {
-    const hipError_t attr = fused_attr<R, RB>();
+    const hipError_t attr = DEF ? hipSuccess : fused_attr<R, RB>();
     if (attr != hipSuccess) return attr;
     // the first pass may store every tile; otherwise a pass runs over the tiles that hold amplitude
     const bool fill = init >= 0 && h.zero_fill;
@@ -878,6 +877,12 @@ static hipError_t launch_t(R *psi, int n, int S, const PassDesc &h, int pass_ind
     hipLaunchKernelGGL((k_fused<R, RB, UNI, BLK, ZV, MIX>), dim3(blocks), dim3(threads), lds, st, psi, n, S, pass_index, \
                        rec_cap, init, basis, blocal, dyn, prog.passes, prog.stages, prog.rounds, prog.ops,         \
                        (const cxf<R> *)rec, (const cxf<R> *)wtab, otab, ovl, slot_base, slots)
+    if constexpr (DEF) {
+        const hipError_t e = fused_attr_one<R, RB, false, false, 7, true>();
+        if (e != hipSuccess) return e;
+        QS_FUSED_LAUNCH_M(false, false, 7, true);
+        return hipGetLastError();
+    } else {
 #define QS_FUSED_LAUNCH(UNI, ZV)                                                                               \
     do {                                                                                                       \
         if (h.mixed_ops) QS_FUSED_LAUNCH_M(UNI, false, ZV, true);                                              \
@@ -898,8 +903,7 @@ static hipError_t launch_t(R *psi, int n, int S, const PassDesc &h, int pass_ind
         if (h.shear) QS_FUSED_LAUNCH(false, 6);
         else QS_FUSED_LAUNCH(false, 4);
     } else if (h.zin_ops == 5) {
-        if (RB >= 3 && h.defer) QS_FUSED_LAUNCH_M(false, false, (RB >= 3 ? 7 : 5), true);
-        else QS_FUSED_LAUNCH_M(false, false, 5, true);
+        QS_FUSED_LAUNCH_M(false, false, 5, true);
     } else if (h.zin_ops == 2) {
         if (h.uni_kernel) QS_FUSED_LAUNCH(true, 2);
         else QS_FUSED_LAUNCH(false, 2);
@@ -913,6 +917,7 @@ static hipError_t launch_t(R *psi, int n, int S, const PassDesc &h, int pass_ind
 #undef QS_FUSED_LAUNCH
 #undef QS_FUSED_LAUNCH_M
     return hipGetLastError();
+    }
 }
 
 // One amplitude type's fused passes (fused_c64.hip, fused_c128.hip).
@@ -923,7 +928,9 @@ hipError_t fused_attributes()
     if ((e = fused_attr<R, 1>()) != hipSuccess || (e = fused_attr<R, 2>()) != hipSuccess ||
         (e = fused_attr<R, 3>()) != hipSuccess)
         return e;
-    return fused_attr<R, 4>();
+    if ((e = fused_attr<R, 4>()) != hipSuccess || (e = fused_attr_one<R, 3, false, false, 7, true>()) != hipSuccess)
+        return e;
+    return fused_attr_one<R, 4, false, false, 7, true>();
 }
 
 template <typename R>
@@ -935,11 +942,20 @@ hipError_t fused_launch(R *p, int n, int S, const PassDesc &h, int pass_index, i
     case RB:                                                                                                        \
         return launch_t<R, RB>(p, n, S, h, pass_index, rec_cap, init, basis, dyn, prog, rec, wtab, otab, lds, st, ovl, \
                                slot_base, slots);
-    switch (h.RB) {
+    // (The collecting variants last, so that their kernels are compiled, and placed, after the others: ahead
+    // of the 16-register kernels, whose code is larger than the instruction cache, the 8-register one cost
+    // brickwork passes at n = 26, complex<double>, 0.7 %.)
+    switch (h.defer ? h.RB + 8 : h.RB) {
         QS_FUSED_CASE(1)
         QS_FUSED_CASE(2)
         QS_FUSED_CASE(3)
         QS_FUSED_CASE(4)
+    case 11:
+        return launch_t<R, 3, true>(p, n, S, h, pass_index, rec_cap, init, basis, dyn, prog, rec, wtab, otab, lds, st,
+                                    ovl, slot_base, slots);
+    case 12:
+        return launch_t<R, 4, true>(p, n, S, h, pass_index, rec_cap, init, basis, dyn, prog, rec, wtab, otab, lds, st,
+                                    ovl, slot_base, slots);
     }
 #undef QS_FUSED_CASE
     return hipErrorInvalidValue;
