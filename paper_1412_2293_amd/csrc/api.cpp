@@ -1243,7 +1243,7 @@ qs_status qs_plan_describe(const qs_gate *gates, int n_gates, int n, qs_dtype dt
     I("RB", pl.prog.RB);
     I("mfma", pl.mfma ? 1 : 0);
     I("run_bits", pl.run_bits);
-    if (pl.fused) I("stage_rec_cap", stage_rec_area(dt, pl.prog.K));
+    if (pl.fused) I("stage_rec_cap", stage_rec_cap(dt, pl.prog.K));
     {
         const double cost = pl.fused ? model_cost_fused(pl.prog, n, dt, kModelSlots, pl.run_bits)
                                      : model_cost_unfused(gates, n_gates, n, dt, kModelSlots);

@@ -308,8 +308,10 @@ __global__ void __launch_bounds__(128) k_pass_prep(int S, int pass0, ProgramDev 
                     if ((y >> k) & 1) w = dmul(w, ptid[5 + k]);
                 put(b + 36 + y, w);
             }
-            put(b + 52, make_double2(1.0, 0.0));
-            put(b + 53, ptid[9]);
+            if (pd->K - pd->RB > 9) {
+                put(b + 52, make_double2(1.0, 0.0));
+                put(b + 53, ptid[9]);
+            }
         }
     } else if (op.type == OP_U2) {
         const double *m = gates[op.gate].m;
@@ -319,23 +321,13 @@ __global__ void __launch_bounds__(128) k_pass_prep(int S, int pass0, ProgramDev 
     }
 }
 
-// Record entries per stage that the planner counts: 8 KiB of records (a stage bounds the descriptor
-// ranges the kernel walks between two plan boundaries); 0 when the tile does not fit the 160 KiB of
-// LDS.
+// Record entries per stage: 8 KiB of records (a stage bounds the descriptor ranges the kernel
+// walks between two plan boundaries); 0 when the tile does not fit the 160 KiB of LDS.
 int stage_rec_cap(qs_dtype dt, int K)
 {
     const size_t cxs = dt == QS_C64 ? 8 : 16;
     if ((size_t(1) << K) * cxs > 160 * 1024) return 0;
     return (int)(8192 / cxs);
-}
-
-// Record entries that a stage can have: the planner counts kPhaseTable - 2 entries for a phase block,
-// so that a stage holds what it held before the two factors of thread-id bit 9 were added, and at most
-// 1024 / 52 blocks go over by two each.
-int stage_rec_area(qs_dtype dt, int K)
-{
-    const int cap = stage_rec_cap(dt, K);
-    return cap ? cap + 64 : 0;
 }
 
 // LDS of one block: its tile.

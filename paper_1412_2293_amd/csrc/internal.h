@@ -44,7 +44,10 @@ void clear_error();
 // ---------------------------------------------------------------------------------------
 constexpr int kMaxTileBits = 15;
 constexpr int kMaxRegBits = 4;
-constexpr int kPhaseTable = 4 + 32 + 16 + 2;   // reg + lo + hi + top entries of a phase block
+constexpr int kPhaseTable = 4 + 32 + 16;   // reg + lo + hi entries of a phase block
+
+// Entries of a phase block before its outer phases, with 2^threads_log threads per tile.
+__host__ __device__ inline int phase_table(int threads_log) { return kPhaseTable + (threads_log > 9 ? 2 : 0); }
 
 struct RoundDesc {
     uint32_t reg_mask;            // tile-local bits held in registers during this round
@@ -382,9 +385,9 @@ hipError_t launch_pass_jobs(qs_dtype dt, int S, const PassDesc *pass_host, int c
                             const void *rec, void *wt, const PassAreas &ar, int64_t init, int64_t basis,
                             const RunParams *dyn, hipStream_t st);
 size_t fused_lds_bytes(qs_dtype dt, int K);
-// Record entries per stage that fit next to a tile of 2^K amplitudes (two tiles per CU).
+// Record entries per stage at most (0: no tile of 2^K amplitudes fits the LDS); whole-state programs stage
+// that many beside their tile.
 int stage_rec_cap(qs_dtype dt, int K);
-int stage_rec_area(qs_dtype dt, int K);
 
 // Fixed rank: Gram of the 2r half-columns; partial blocks then a fixed-order final sum.
 size_t fr_gram_partials_doubles(int n, int r);

@@ -487,6 +487,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
             for (int j = K - 1; j >= 0 && __builtin_popcount(m) < RB; --j) m |= 1u << j;
             return m;
         };
+        const int table = phase_table(K - RB);
         auto costs = [&](int i, int &rec_c, int &jobs_c, int &obits_c) {
             const PG &x = pg[i];
             rec_c = jobs_c = obits_c = 0;
@@ -500,7 +501,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                     int no = 0;
                     for (auto &at : att)
                         if (local_of[at.cond] < 0) ++no;
-                    rec_c += kPhaseTable - 2 + no;   // (without the factors of thread-id bit 9)
+                    rec_c += table + no;
                     if (no) {
                         ++jobs_c;
                         obits_c += no;
@@ -663,7 +664,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                         int n_outer = 0;
                         for (auto &at : att)
                             if (local_of[at.cond] < 0) ++n_outer;
-                        rec += kPhaseTable + n_outer;
+                        rec += table + n_outer;
                         if (post) op.post_rec = block; else op.pre_rec = block;
                         int outer_k = 0;
                         int bits_off = (int)P.obits.size();
@@ -675,7 +676,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                             if (j < 0) {
                                 pr.kind = PR_OUTER;
                                 pr.bit = at.cond;
-                                pr.slot_entry = block + kPhaseTable + outer_k++;
+                                pr.slot_entry = block + table + outer_k++;
                                 P.obits.push_back(at.cond);
                             } else if ((lcls >> j) & 1u) {
                                 pr.kind = PR_BASIS;
@@ -705,7 +706,7 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
                         if (n_outer > 0) {
                             OuterJob jb{};
                             jb.op = (int)P.ops.size();
-                            jb.rec_off = block + kPhaseTable;
+                            jb.rec_off = block + table;
                             jb.bits_off = bits_off;
                             jb.n = n_outer;
                             if (post) op.post_job = (int)P.jobs.size() - pd.job_begin;

@@ -236,7 +236,7 @@ __global__ void __launch_bounds__((kStateThreads<R, RB>))
 
 size_t state_stage_bytes(qs_dtype dt, int n)
 {
-    return (size_t)kStageSops * sizeof(StateOp) + (size_t)stage_rec_area(dt, n) * 2 * (dt == QS_C64 ? 4 : 8);
+    return (size_t)kStageSops * sizeof(StateOp) + (size_t)stage_rec_cap(dt, n) * 2 * (dt == QS_C64 ? 4 : 8);
 }
 
 bool state_shape(qs_dtype dt, int n, int RB)
