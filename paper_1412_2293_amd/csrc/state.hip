@@ -258,12 +258,20 @@ int state_reg_bits(qs_dtype dt, int n)
     return 0;
 }
 
+// One-time opt-in to the full 160 KiB of LDS.
+template <typename R, int RB, bool PLAIN>
+static hipError_t state_attr_one()
+{
+    static const hipError_t attr = hipFuncSetAttribute((const void *)k_state<R, RB, PLAIN>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    return attr;
+}
+
 template <typename R, int RB, bool PLAIN>
 static hipError_t state_launch_t(R *psi, qs_dtype dt, int n, int S, int pass_index, int64_t init, const RunParams *dyn,
                                  ProgramDev prog, const void *rec, hipStream_t st)
 {
-    static const hipError_t attr = hipFuncSetAttribute((const void *)k_state<R, RB, PLAIN>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    const hipError_t attr = state_attr_one<R, RB, PLAIN>();
     if (attr != hipSuccess) return attr;
     const size_t tile = fused_lds_bytes(dt, n), stage = state_stage_bytes(dt, n);
     const int two = 2 * tile + stage <= 160 * 1024 ? 1 : 0;
@@ -275,13 +283,9 @@ static hipError_t state_launch_t(R *psi, qs_dtype dt, int n, int S, int pass_ind
 hipError_t state_prepare_attributes()
 {
     hipError_t e = hipSuccess;
-#define QS_STATE_ATTR(R, RB)                                                                                        \
-    if (e == hipSuccess)                                                                                            \
-        e = hipFuncSetAttribute((const void *)k_state<R, RB, false>, hipFuncAttributeMaxDynamicSharedMemorySize,    \
-                                160 * 1024);                                                                        \
-    if (e == hipSuccess)                                                                                            \
-        e = hipFuncSetAttribute((const void *)k_state<R, RB, true>, hipFuncAttributeMaxDynamicSharedMemorySize,     \
-                                160 * 1024);
+#define QS_STATE_ATTR(R, RB)                                          \
+    if (e == hipSuccess) e = state_attr_one<R, RB, false>();          \
+    if (e == hipSuccess) e = state_attr_one<R, RB, true>();
     QS_STATE_ATTR(float, 2) QS_STATE_ATTR(float, 3) QS_STATE_ATTR(float, 4)
     QS_STATE_ATTR(double, 2) QS_STATE_ATTR(double, 3) QS_STATE_ATTR(double, 4)
 #undef QS_STATE_ATTR
