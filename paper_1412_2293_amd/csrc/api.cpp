@@ -118,8 +118,8 @@ struct qs_fr_s {
     void *V;
     hipStream_t st;
     double log_trace;
-    double *scratch;     // device: gram partials | gram out | coef | overlap partials | out | table
-    size_t off_gram, off_coef, off_ovp, off_ovo, off_tab;
+    double *scratch;     // device: gram partials | coef | overlap partials | out | table
+    size_t off_coef, off_ovp, off_ovo, off_tab;
     double *host;        // pinned staging: gram, then coef (kFrHostGram doubles each)
     double *host_dev;    // its device address (the Gram's final sum writes there)
 };
@@ -1878,8 +1878,6 @@ qs_status qs_fr_create(int n, int r, qs_dtype dt, void *buf, size_t bytes, void 
     f->log_trace = 0.0;
     size_t off = 0;
     off += align256(fr_gram_partials_doubles(n, r) * 8) / 8;
-    f->off_gram = off;
-    off += kFrHostGram;
     f->off_coef = off;
     off += kFrHostGram;
     f->off_ovp = off;
