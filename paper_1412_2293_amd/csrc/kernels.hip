@@ -833,9 +833,12 @@ __global__ void __launch_bounds__(kRedThreads) k_overlap_partial(const R *ref, c
     }
 }
 
-// One workgroup per slot.  Each thread keeps four partials in flight (a slot of 2^26 amplitudes
-// has 2^14 of them: with one at a time the sum waited 64 load latencies, 32 us), and the sums meet
-// over the lanes of each wave, then over the waves, in a fixed order.
+// One workgroup per slot, with as many threads as the slot has partials (whole waves, at most
+// kFinalThreads; many slots of few partials: 3001 slots of one, 5 us with one wave each, 22 with sixteen).
+// Each thread keeps four partials in flight (a slot of 2^26 amplitudes has 2^14 of them: with one at a
+// time the sum waited 64 load latencies, 32 us), and the sums meet over the lanes of each wave, then over
+// the waves, in a fixed order (a wave without partials would add zero, so it does not depend on the
+// threads).
 constexpr int kFinalThreads = 1024;
 
 template <typename R>
@@ -845,17 +848,17 @@ __global__ void __launch_bounds__(kFinalThreads) k_overlap_final(const R *psi, i
 {
     __shared__ double sh[3][kFinalThreads / 64];
     if (dyn) marked = dyn->marked;
-    const int slot = blockIdx.x, t = (int)threadIdx.x;
+    const int slot = blockIdx.x, t = (int)threadIdx.x, nthr = (int)blockDim.x;
     const int nb = 1 << log_blocks;
     const double *q = partials + (uint64_t)slot * nb * 3;
     double v[3] = {0, 0, 0};
-    for (int b = t; b < nb; b += 4 * kFinalThreads) {
+    for (int b = t; b < nb; b += 4 * nthr) {
         double x[4][3];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                const int i = b + u * kFinalThreads;
+                const int i = b + u * nthr;
                 x[u][k] = i < nb ? q[(uint64_t)i * 3 + k] : 0.0;
             }
 #pragma unroll
@@ -872,7 +875,7 @@ __global__ void __launch_bounds__(kFinalThreads) k_overlap_final(const R *psi, i
     double *o = out + (uint64_t)slot * 5;
     if (t < 3) {
         double a = 0.0;
-        for (int w = 0; w < kFinalThreads / 64; ++w) a += sh[t][w];
+        for (int w = 0; w < nthr / 64; ++w) a += sh[t][w];
         o[t] = a;
     } else if (t < 5) {
         o[t] = marked >= 0 ? (double)psi[((uint64_t)slot << (n + 1)) + 2 * marked + (t - 3)] : 0.0;
@@ -1394,16 +1397,23 @@ size_t reduce_partials_doubles(int n, int S)
     return a > b ? a : b;
 }
 
+template <typename R>
+static void overlap_final(const void *psi, int n, int S, int log_blocks, int64_t marked, const double *partials,
+                          double *out, hipStream_t st, const RunParams *dyn)
+{
+    const unsigned threads = std::min(std::max(1u << log_blocks, 64u), (unsigned)kFinalThreads);
+    hipLaunchKernelGGL(k_overlap_final<R>, dim3((unsigned)S), dim3(threads), 0, st, (const R *)psi, n, log_blocks, marked,
+                       partials, out, dyn);
+}
+
 hipError_t launch_overlap_final(const void *psi, qs_dtype dt, int n, int S, int log_blocks, int64_t marked,
                                 const double *partials, double *out, hipStream_t st, const RunParams *dyn)
 {
     TimedLaunch tl("reduce", (double)((uint64_t)S << log_blocks) * 3 * sizeof(double), st);
     if (dt == QS_C64)
-        hipLaunchKernelGGL(k_overlap_final<float>, dim3(S), dim3(kFinalThreads), 0, st, (const float *)psi, n,
-                           log_blocks, marked, partials, out, dyn);
+        overlap_final<float>(psi, n, S, log_blocks, marked, partials, out, st, dyn);
     else
-        hipLaunchKernelGGL(k_overlap_final<double>, dim3(S), dim3(kFinalThreads), 0, st, (const double *)psi, n,
-                           log_blocks, marked, partials, out, dyn);
+        overlap_final<double>(psi, n, S, log_blocks, marked, partials, out, st, dyn);
     return hipGetLastError();
 }
 
@@ -1419,14 +1429,12 @@ hipError_t launch_overlaps(const void *ref_psi, int ref_slot, const void *psi, q
         const float *ref = (const float *)ref_psi + ((uint64_t)ref_slot << (n + 1));
         hipLaunchKernelGGL((k_overlap_partial<float, false>), dim3(nblk), dim3(kRedThreads), 0, st, ref,
                            (const float *)psi, n, lb, partials);
-        hipLaunchKernelGGL(k_overlap_final<float>, dim3(S), dim3(kFinalThreads), 0, st,
-                           (const float *)psi, n, lb, marked, partials, out, dyn);
+        overlap_final<float>(psi, n, S, lb, marked, partials, out, st, dyn);
     } else {
         const double *ref = (const double *)ref_psi + ((uint64_t)ref_slot << (n + 1));
         hipLaunchKernelGGL((k_overlap_partial<double, false>), dim3(nblk), dim3(kRedThreads), 0, st, ref,
                            (const double *)psi, n, lb, partials);
-        hipLaunchKernelGGL(k_overlap_final<double>, dim3(S), dim3(kFinalThreads), 0, st,
-                           (const double *)psi, n, lb, marked, partials, out, dyn);
+        overlap_final<double>(psi, n, S, lb, marked, partials, out, st, dyn);
     }
     return hipGetLastError();
 }
@@ -1439,13 +1447,11 @@ hipError_t launch_fidelity(const void *a, const void *b, qs_dtype dt, int n, dou
     if (dt == QS_C64) {
         hipLaunchKernelGGL((k_overlap_partial<float, true>), dim3(1u << lb), dim3(kRedThreads), 0, st, (const float *)a,
                            (const float *)b, n, lb, partials);
-        hipLaunchKernelGGL(k_overlap_final<float>, dim3(2), dim3(kFinalThreads), 0, st, (const float *)b, n, lb, -1,
-                           partials, out, (const RunParams *)nullptr);
+        overlap_final<float>(b, n, 2, lb, -1, partials, out, st, nullptr);
     } else {
         hipLaunchKernelGGL((k_overlap_partial<double, true>), dim3(1u << lb), dim3(kRedThreads), 0, st,
                            (const double *)a, (const double *)b, n, lb, partials);
-        hipLaunchKernelGGL(k_overlap_final<double>, dim3(2), dim3(kFinalThreads), 0, st, (const double *)b, n, lb, -1,
-                           partials, out, (const RunParams *)nullptr);
+        overlap_final<double>(b, n, 2, lb, -1, partials, out, st, nullptr);
     }
     return hipGetLastError();
 }
