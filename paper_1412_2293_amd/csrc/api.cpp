@@ -1020,7 +1020,10 @@ static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char
     QS_HIP(launch_noise_table(gdev, n_gates, S, na, tab, st));
     if (prep.fused && !P.chain_off.empty()) {
         const int32_t *off = (const int32_t *)(B + L.chains);
-        QS_HIP(launch_phase_chains(tab, S, off + P.chain_off.size(), off, (int)P.chain_off.size() - 1, st));
+        int longest = 0;
+        for (size_t k = 1; k < P.chain_off.size(); ++k)
+            longest = std::max(longest, (int)(P.chain_off[k] - P.chain_off[k - 1]));
+        QS_HIP(launch_phase_chains(tab, S, off + P.chain_off.size(), off, (int)P.chain_off.size() - 1, longest, st));
     }
     // fused runs make the initial state inside their first pass
     if (!prep.fused || P.passes.empty()) QS_HIP(launch_init_basis(psi, dt, n, S, init_index, st, dyn));

@@ -86,7 +86,7 @@ __global__ void k_block_prep(int S, int round_begin, int n_rounds, int rec_size,
 }
 
 // ---------------------------------------------------------------------------------------
-// Phase chains (one wave per chain and slot, FP64).  Along a chain of one-qubit gates on
+// Phase chains (W lanes per chain and slot, FP64).  Along a chain of one-qubit gates on
 // one wire, each inner gate's matrix M (with the phase c carried from the gate before it
 // multiplied into its |1> column) is factored as M = p * diag(1, b) * Rm * diag(1, d) with
 // unit p, b, d and Rm real.  Its row is rewritten as Rm in words 0, 2, 4, 6 and the input
@@ -97,20 +97,23 @@ __global__ void k_block_prep(int S, int round_begin, int n_rounds, int rec_size,
 // divided out.  For a unitary M (M10 = -e^{it} conj(M01), M11 = e^{it} conj(M00)) the
 // divided-out entries are real, so the factors reproduce M; a phase taken from a zero or
 // rounding-sized entry only affects entries of that size.  (phase(0) = 1.)
-// c drops out of b, so the lanes factor 64 gates at once, take c from the lane before and multiply
-// the global phase in a tree (60 gates: 74 us as one thread's walk, 4 us here).
+// c drops out of b, so the lanes factor W gates at once, take c from the lane before and multiply
+// the global phase in a tree (60 gates, 64 lanes: 74 us as one thread's walk, 4 us here).  The fewest
+// lanes that hold the longest chain are taken: 42014 chains of 10 gates, 38 us with 64 lanes each and 17
+// with 16.  A wider tree would only multiply by ones, so the results do not depend on W.
 // ---------------------------------------------------------------------------------------
+template <int W>
 __global__ void __launch_bounds__(256) k_phase_chains(double *tab, int S, const int32_t *__restrict__ chain_gates,
                                                       const int32_t *__restrict__ chain_off, int n_chains)
 {
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / W;
     if (i >= (int64_t)n_chains * S) return;
-    const int lane = (int)(threadIdx.x & 63u);
+    const int lane = (int)threadIdx.x % W;
     const int c = (int)(i / S), s = (int)(i % S);
     const int kb = chain_off[c], ke = chain_off[c + 1];
     const double2 one = make_double2(1.0, 0.0);
     double2 carry = one, glob = one;
-    for (int k0 = kb; k0 < ke; k0 += 64) {
+    for (int k0 = kb; k0 < ke; k0 += W) {
         const int k = k0 + lane;
         const bool in = k < ke, inner = k < ke - 1;
         double *t = tab + ((int64_t)chain_gates[in ? k : ke - 1] * S + s) * 8;
@@ -120,11 +123,11 @@ __global__ void __launch_bounds__(256) k_phase_chains(double *tab, int S, const 
         const double2 b = hypot(m11.x, m11.y) >= hypot(m10.x, m10.y)
                               ? dmul(dunit(m11), dconj(q))
                               : dmul(make_double2(-1.0, 0.0), dmul(dunit(m10), dconj(p)));
-        double2 cin = make_double2(__shfl_up(b.x, 1, 64), __shfl_up(b.y, 1, 64));
+        double2 cin = make_double2(__shfl_up(b.x, 1, W), __shfl_up(b.y, 1, W));
         if (lane == 0) cin = carry;
         double2 g = inner ? p : one;
-        for (int off = 32; off > 0; off >>= 1)
-            g = dmul(g, make_double2(__shfl_xor(g.x, off, 64), __shfl_xor(g.y, off, 64)));
+        for (int off = W / 2; off > 0; off >>= 1)
+            g = dmul(g, make_double2(__shfl_xor(g.x, off, W), __shfl_xor(g.y, off, W)));
         glob = dmul(glob, g);
         if (inner) {
             const double2 d = dmul(cin, dmul(q, dconj(p))), pb = dmul(p, b);
@@ -145,18 +148,24 @@ __global__ void __launch_bounds__(256) k_phase_chains(double *tab, int S, const 
                 t[2 * j + 1] = o[j].y;
             }
         }
-        carry = make_double2(__shfl(b.x, 63, 64), __shfl(b.y, 63, 64));
+        carry = make_double2(__shfl(b.x, W - 1, W), __shfl(b.y, W - 1, W));
     }
 }
 
 hipError_t launch_phase_chains(double *tab, int S, const int32_t *chain_gates, const int32_t *chain_off,
-                               int n_chains, hipStream_t st)
+                               int n_chains, int longest, hipStream_t st)
 {
     const int64_t tot = (int64_t)n_chains * S;
     if (tot <= 0) return hipSuccess;
     TimedLaunch tl("chains", (double)tot * 64.0, st);
-    hipLaunchKernelGGL(k_phase_chains, dim3((unsigned)((tot + 3) / 4)), dim3(256), 0, st, tab, S, chain_gates, chain_off,
-                       n_chains);
+#define QS_CHAINS(W)                                                                                          \
+    hipLaunchKernelGGL(k_phase_chains<W>, dim3((unsigned)((tot * W + 255) / 256)), dim3(256), 0, st, tab, S,  \
+                       chain_gates, chain_off, n_chains)
+    if (longest <= 8) QS_CHAINS(8);
+    else if (longest <= 16) QS_CHAINS(16);
+    else if (longest <= 32) QS_CHAINS(32);
+    else QS_CHAINS(64);
+#undef QS_CHAINS
     return hipGetLastError();
 }
 

@@ -260,8 +260,9 @@ hipError_t launch_noise_table(const qs_gate *gates_dev, int n_gates, int S, Nois
                               double *tab, hipStream_t st);
 // Rewrites the noise-table rows of the phase chains (chain layout in the fused path's
 // documentation); chain_gates / chain_off in device memory, n_chains >= 1.
+// longest: the gates of the longest chain.
 hipError_t launch_phase_chains(double *tab, int S, const int32_t *chain_gates, const int32_t *chain_off,
-                               int n_chains, hipStream_t st);
+                               int n_chains, int longest, hipStream_t st);
 hipError_t launch_noise_draw(uint64_t seed, uint32_t request, uint32_t stream,
                              const uint32_t *sites, int n_sites, uint32_t traj_base, int n_traj,
                              double *out, hipStream_t st);
