@@ -228,16 +228,21 @@ constexpr double kShearMin = 0x1p-60;
 // One thread per (slot, op), then one wave per (slot, stage) for the products of the stages' factors
 // alpha.  blockIdx.y: the pass, pass0 + blockIdx.y of the program, with its own record area; a launch
 // per pass took 5 us of a chain of loads for 0.2 ms passes (Grover n = 20), the same as one for 32.
+// Few threads, each with a chain of loads and products: the descriptors are read together, and no bound on
+// the workgroup is given, with which the compiler moves the factors from scratch memory to the LDS (QFT
+// n = 8, complex<float>, 3001 slots: 24.6 us with a bound of 128 threads, 16.0 without).
 template <typename R>
-__global__ void __launch_bounds__(128) k_pass_prep(int S, int pass0, ProgramDev prog, const double *tab,
-                                                   const qs_gate *gates, char *rec_base, uint64_t basis,
-                                                   const RunParams *dyn, PassAreas ar)
+__global__ void k_pass_prep(int S, int pass0, ProgramDev prog, const double *tab, const qs_gate *gates, char *rec_base,
+                            uint64_t basis, const RunParams *dyn, PassAreas ar)
 {
     const PassDesc *pd = prog.passes + pass0 + blockIdx.y;
-    if (pd->expand) return;   // (launch_expand_prep)
-    const int op_begin = pd->op_begin, n_ops = pd->op_end - op_begin, rec_size = pd->rec_size;
+    const int expand = pd->expand, op_begin = pd->op_begin, n_ops = pd->op_end - op_begin, rec_size = pd->rec_size;
+    const int threads_log = pd->K - pd->RB;
     const int stage_begin = pd->stage_begin, n_stages = pd->stage_end - stage_begin;
     const int op_blocks = (int)(((int64_t)n_ops * S + 127) / 128);
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const OpDesc op = prog.ops[i < (int64_t)n_ops * S ? op_begin + (int)(i % n_ops) : 0];
+    if (expand) return;   // (launch_expand_prep)
     cxf<R> *rec_all = reinterpret_cast<cxf<R> *>(rec_base + blockIdx.y * ar.rec_stride);
     if ((int)blockIdx.x >= op_blocks) {
         const int64_t w = (int64_t)((int)blockIdx.x - op_blocks) * 2 + (threadIdx.x >> 6);
@@ -258,11 +263,9 @@ __global__ void __launch_bounds__(128) k_pass_prep(int S, int pass0, ProgramDev 
             rec_all[(size_t)slot * rec_size + sd.scale_rec] = sheared ? cxf<R>{(R)f, (R)1} : cxf<R>{(R)1, (R)0};
         return;
     }
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (int64_t)n_ops * S) return;
     if (dyn) basis = dyn->init;
-    const int slot = (int)(i / n_ops), ol = (int)(i % n_ops);
-    const OpDesc op = prog.ops[op_begin + ol];
+    const int slot = (int)(i / n_ops);
     cxf<R> *blk = rec_all + (size_t)slot * rec_size;
     cxf<R> *rec = blk + op.rec;
     auto tabc = [&](int g) {
@@ -317,7 +320,7 @@ __global__ void __launch_bounds__(128) k_pass_prep(int S, int pass0, ProgramDev 
                     if ((y >> k) & 1) w = dmul(w, ptid[5 + k]);
                 put(b + 36 + y, w);
             }
-            if (pd->K - pd->RB > 9) {
+            if (threads_log > 9) {
                 put(b + 52, make_double2(1.0, 0.0));
                 put(b + 53, ptid[9]);
             }
