@@ -262,13 +262,38 @@ int state_reg_bits(qs_dtype dt, int n)
     return 0;
 }
 
-// One-time opt-in to the full 160 KiB of LDS.
+// One-time opt-in to the full 160 KiB of LDS, which also notes the waves per CU that the variant's registers
+// allow.
+template <typename R, int RB, bool PLAIN>
+static int state_waves = 0;
+
 template <typename R, int RB, bool PLAIN>
 static hipError_t state_attr_one()
 {
-    static const hipError_t attr = hipFuncSetAttribute((const void *)k_state<R, RB, PLAIN>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    static const hipError_t attr = [] {
+        hipFuncAttributes fa;
+        const hipError_t e = hipFuncGetAttributes(&fa, (const void *)k_state<R, RB, PLAIN>);
+        if (e != hipSuccess) return e;
+        state_waves<R, RB, PLAIN> = 4 * std::min(8, 512 / std::max(fa.numRegs, 1));
+        return hipFuncSetAttribute((const void *)k_state<R, RB, PLAIN>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   160 * 1024);
+    }();
     return attr;
+}
+
+// Whether the state is exchanged through two LDS buffers in turn (one barrier per exchange) or one (two
+// barriers).  Two where every slot's workgroup runs at once with two buffers, or where the registers admit no
+// more workgroups to a CU with one; else one, so that more workgroups share a CU (random pairs n = 13, 10
+// layers, 3001 slots, complex<float>: 1298 us with two, 985 with one; n = 8 297 and 253; n = 11,
+// complex<double>, where the registers admit two either way, Grover: 638 and 671).  The results are the same.
+static bool state_two_buffers(size_t tile, size_t stage, int threads, int waves, int S)
+{
+    constexpr size_t lds = 160 * 1024;
+    constexpr int cus = 256;
+    if (2 * tile + stage > lds) return false;
+    const int by_regs = waves * 64 / threads;
+    const int two = std::min((int)(lds / (2 * tile + stage)), by_regs), one = std::min((int)(lds / (tile + stage)), by_regs);
+    return one <= two || S <= cus * two;
 }
 
 template <typename R, int RB, bool PLAIN>
@@ -278,9 +303,10 @@ static hipError_t state_launch_t(R *psi, qs_dtype dt, int n, int S, int pass_ind
     const hipError_t attr = state_attr_one<R, RB, PLAIN>();
     if (attr != hipSuccess) return attr;
     const size_t tile = fused_lds_bytes(dt, n), stage = state_stage_bytes(dt, n);
-    const int two = 2 * tile + stage <= 160 * 1024 ? 1 : 0;
-    hipLaunchKernelGGL((k_state<R, RB, PLAIN>), dim3((unsigned)S), dim3(std::max(64u, 1u << (n - RB))), (tile << two) + stage, st, psi, n,
-                       pass_index, init, dyn, prog.passes, prog.stages, prog.rounds, prog.sops, (const cxf<R> *)rec, two);
+    const unsigned threads = std::max(64u, 1u << (n - RB));
+    const int two = state_two_buffers(tile, stage, (int)threads, state_waves<R, RB, PLAIN>, S) ? 1 : 0;
+    hipLaunchKernelGGL((k_state<R, RB, PLAIN>), dim3((unsigned)S), dim3(threads), (tile << two) + stage, st, psi, n, pass_index,
+                       init, dyn, prog.passes, prog.stages, prog.rounds, prog.sops, (const cxf<R> *)rec, two);
     return hipGetLastError();
 }
 
