@@ -264,14 +264,15 @@ bool state_shape(qs_dtype dt, int n, int RB)
     return fused_lds_bytes(dt, n) + state_stage_bytes(dt, n) <= 160 * 1024;
 }
 
-// Register bits of the automatic plan: the fewest whose workgroup is allowed (random layers, 50
-// trajectories: n = 12 complex<float> 334 us with 3 against 380 with 4, complex<double> 438 against
-// 461; n = 11 complex<float> 300 with 2, 310 with 3, 359 with 4; Grover n = 8 complex<double> 169
-// with 2, 197 with 3, 257 with 4).
+// Register bits of the automatic plan: the fewest whose workgroup is allowed and, up to 3, has at most 256
+// threads (random layers, 50 trajectories: n = 12 complex<float> 334 us with 3 against 380 with 4, complex<double>
+// 438 against 461; Grover n = 8 complex<double> 169 with 2, 197 with 3, 257 with 4.  Random pairs n = 11, 60
+// layers, with 2 and with 3, complex<float>: 2 slots 425 us and 450, 3001 slots 2320 and 1860; complex<double>:
+// 494 and 505, 3250 and 3050).
 int state_reg_bits(qs_dtype dt, int n)
 {
     for (int rb = 2; rb <= kMaxRegBits; ++rb)
-        if (state_shape(dt, n, rb)) return rb;
+        if (state_shape(dt, n, rb) && (rb >= 3 || n - rb <= 8)) return rb;
     return 0;
 }
 
