@@ -572,6 +572,23 @@ struct Plan {
     qs::Program prog;
 };
 
+// Whether a circuit has too many dense two-qubit gates for a whole-state program, which reads a gate's 16
+// entries from the LDS for every thread's few amplitudes, where a fused pass of the same tile has them in
+// scalar registers: more than one in eight, from 10 qubits (complex<float>; 11 complex<double>) on
+// (3001 slots of 300 random gates, a third of them dense: n = 11, complex<float>, 853 us as a pass and 1130
+// as a whole-state program; n = 8 649 and 461; without dense gates n = 11, 10 layers, 505 and 495).
+bool state_dense(const qs_gate *gates, int n_gates, int n, qs_dtype dt)
+{
+    if (n < (dt == QS_C64 ? 10 : 11)) return false;
+    int dense = 0, ops = 0;
+    for (int g = 0; g < n_gates; ++g) {
+        const int k = gates[g].kind;
+        dense += k == QS_G_U2 || k == QS_G_CNOT;
+        ops += k == QS_G_U1 || k == QS_G_U2 || k == QS_G_CNOT;
+    }
+    return 8 * dense > ops;
+}
+
 qs_status fused_plan_for(const qs_gate *gates, int n_gates, int n, qs_dtype dt, int K, int RB, int run,
                          Plan &out, bool mfma = false)
 {
@@ -585,11 +602,13 @@ qs_status fused_plan_for(const qs_gate *gates, int n_gates, int n, qs_dtype dt, 
         K = n;   // the whole state is one tile: the circuit runs as one launch
         if (RB > K) RB = K;
     }
-    const bool state = K == n && !mfma && state_shape(dt, n, RB);
+    const bool shape = K == n && !mfma && state_shape(dt, n, RB);
     // wide register tiles (16 complex<float>, 8 or 16 complex<double>) run 256-thread blocks
     // (more only in the shape that the automatic plan gives a whole-state program, given as such)
-    if (!(state && exact && RB == state_reg_bits(dt, n)) && (RB == 4 || (dt == QS_C128 && RB == 3)) && K - RB > 8)
+    const bool wide = (RB == 4 || (dt == QS_C128 && RB == 3)) && K - RB > 8;
+    if (wide && !(shape && exact && RB == state_reg_bits(dt, n)))
         return fail(QS_EINVAL, "plan: this register tile allows at most 256 threads (tile_bits - reg_bits <= 8)");
+    const bool state = shape && (wide || !state_dense(gates, n_gates, n, dt));
     out.K = K;
     out.RB = RB;
     out.run_bits = run;
@@ -679,6 +698,44 @@ double model_cost_fused(const Program &P, int n, qs_dtype dt, int S, int run_bit
     return total + kModelLaunch * (double)P.passes.size() / std::max(S, 1);
 }
 
+// Seconds per slot on a full chip, without launches: as model_cost_fused, but a pass works on the tiles that
+// hold amplitude only.  A whole-state program reaches more of the issue rate than a pass (complex<float> 0.96 of
+// the modelled time, complex<double> 0.85), more so where its tile leaves room for two workgroups on a CU, which
+// hide each other's exchanges (0.72): the factors put the line where the two measured equal.  3001 slots, program
+// against passes, complex<float>: n = 14 (one workgroup), random pairs, 10 layers, 2110 us and 2140, brickwork, 20
+// layers, 3950 and 3500; n = 13 (two), brickwork, 10 layers, 990 and 1170, 2 layers, 340 and 325; complex<double>,
+// n = 13 (one), random pairs, 10 layers, 1990 and 2190, 5 layers, 1110 and 1050.
+static double full_chip_cost(const Program &P, int n, qs_dtype dt)
+{
+    const double N = std::ldexp(1.0, n), amp = (double)amp_bytes(dt), wide = dt == QS_C128 ? 2.0 : 1.0;
+    double total = 0.0;
+    for (size_t pi = 0; pi < P.passes.size(); ++pi) {
+        const PassDesc &pd = P.passes[pi];
+        double per_amp = 20.0;
+        if (pd.expand) {
+            per_amp += 10.0;   // one product per amplitude, whatever the ops
+        } else {
+            per_amp += 6.0 * (pd.round_end - pd.round_begin + 1);
+            for (int oi = pd.op_begin; oi < pd.op_end; ++oi) {
+                const OpDesc &op = P.ops[oi];
+                if (op.type == OP_U1)
+                    per_amp += ((op.flags & OPF_REAL) ? 7.0 : 10.0) + 5.0 * ((op.pre_rec >= 0) + (op.post_rec >= 0));
+                else per_amp += op.type == OP_U2 ? 27.0 : 5.0;
+            }
+        }
+        const double share = std::ldexp(N, -__builtin_popcountll(pd.classical));
+        const double read = pi == 0 ? 0.0 : std::ldexp(1.0, -__builtin_popcount(pd.lclassical));
+        const double alu = share * per_amp * wide / kModelValu;
+        if (pd.state) {
+            total += alu * (2 * fused_lds_bytes(dt, n) <= 150 * 1024 ? 0.72 : dt == QS_C64 ? 0.96 : 0.85);
+            continue;
+        }
+        const double mem = share * (1.0 + read) * amp / kModelHbm;
+        total += std::max(mem, alu) + 0.5 * std::min(mem, alu);
+    }
+    return total;
+}
+
 double model_cost_unfused(const qs_gate *gates, int n_gates, int n, qs_dtype dt, int S)
 {
     const double N = std::ldexp(1.0, n), amp = (double)amp_bytes(dt);
@@ -712,14 +769,19 @@ qs_status autotune_plan(const qs_gate *gates, int n_gates, int n, qs_dtype dt, i
     double best = model_cost_unfused(gates, n_gates, n, dt, S);
     out = Plan();
     out.fused = false;
-    // a state that one workgroup holds runs its whole circuit there: no state traffic between
-    // passes and one launch, whatever the other shapes cost
-    if (const int rb = state_reg_bits(dt, n)) {
-        Plan cand;
-        if (fused_plan_for(gates, n_gates, n, dt, n, rb, 4, cand) == QS_OK) {
-            const double cost = model_cost_fused(cand.prog, n, dt, S, cand.run_bits);
-            if (cost < best * 0.999) {
-                out = std::move(cand);
+    // A state that one workgroup holds runs its whole circuit there: no state traffic between passes and one
+    // launch.  Where other shapes split the state (n > 12), only if it is no slower on a full chip, where its
+    // every gate works on the whole state and a pass's first gates only on the few tiles that hold amplitude
+    // (n = 14, complex<float>, 3001 slots, program against passes: brickwork layers, 10 of them, 2080 us and 1540,
+    // 60 of them, 11340 and 13690; 10 layers and 17 slots 280 and 340: the choice must not depend on the slots).
+    Plan whole;
+    if (const int rb = state_reg_bits(dt, n); rb && !state_dense(gates, n_gates, n, dt)) {
+        if (fused_plan_for(gates, n_gates, n, dt, n, rb, 4, whole) == QS_OK) {
+            const double cost = model_cost_fused(whole.prog, n, dt, S, whole.run_bits);
+            if (cost >= best * 0.999) {
+                whole = Plan();
+            } else if (n <= 12) {
+                out = std::move(whole);
                 if (cost_out) *cost_out = cost;
                 return QS_OK;
             }
@@ -745,6 +807,10 @@ qs_status autotune_plan(const qs_gate *gates, int n_gates, int n, qs_dtype dt, i
                 out = std::move(cand);
             }
         }
+    }
+    if (whole.fused && (!out.fused || full_chip_cost(whole.prog, n, dt) <= full_chip_cost(out.prog, n, dt))) {
+        best = model_cost_fused(whole.prog, n, dt, S, whole.run_bits);
+        out = std::move(whole);
     }
     if (cost_out) *cost_out = best;
     return QS_OK;
