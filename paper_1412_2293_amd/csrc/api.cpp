@@ -562,6 +562,7 @@ struct TrajLayout {
     size_t states, tab, gates, edev, passes, stages, rounds, ops, prefs, jobs, obits, sops, chains, wtab, rec, partials, out,
         dyn, total;
     int window;              // passes that are prepared together
+    int group;               // slots whose records are held at once
     PassAreas areas;
 };
 
@@ -839,6 +840,9 @@ qs_status resolve_plan(const qs_gate *gates, int n_gates, int n, qs_dtype dt, in
     return fused_plan_for(gates, n_gates, n, dt, K, RB, run, out, p && p->mfma == 1);
 }
 
+constexpr size_t kGroupRecBytes = (size_t)64 << 20;
+constexpr size_t kGroupSlots = 512;
+
 TrajLayout traj_layout(int n, qs_dtype dt, int T, int n_gates, const Plan &pl)
 {
     TrajLayout L{};
@@ -864,14 +868,22 @@ TrajLayout traj_layout(int n, qs_dtype dt, int T, int n_gates, const Plan &pl)
     L.chains = take(std::max<size_t>(pl.prog.chain_gates.size() + pl.prog.chain_off.size(), 1) * sizeof(int32_t));
     // per pass of a window: the tiles' outer index bits (at most 2^(n - K) tiles) and the per (slot,
     // tile, outer job) phase products; and the records.  Passes are prepared up to 32 at a time (what
-    // a preparation takes for one: 9 us) where their areas stay within 8 MiB, else one at a time.
+    // a preparation takes for one: 9 us) where their areas stay within 8 MiB, else one at a time.  A whole-state
+    // program's records are those of the whole circuit, up to a few times its noise table, so where passes would
+    // split the circuit (n > 12) the slots run in groups whose records stay within 64 MiB or are those of 512
+    // slots, which two workgroups per CU hold (random pairs n = 13, 60 layers, 3001 slots, complex<float>: 5.1 ms
+    // at once, 5.5 in groups, 6.7 in passes).
     {
         const size_t cxs = 2 * (dt == QS_C64 ? 4 : 8);
         const int tb = pl.fused && n > pl.prog.K ? n - pl.prog.K : 0;
         const size_t entries = ((size_t)S << tb) * (size_t)std::max(pl.prog.max_jobs, 1);
         L.areas.otab_bytes = align256((size_t(1) << tb) * sizeof(uint64_t));
         L.areas.wt_stride = align256(L.areas.otab_bytes + entries * cxs);
-        L.areas.rec_stride = align256((size_t)std::max(pl.prog.max_rec, 1) * S * cxs);
+        const size_t rec = (size_t)std::max(pl.prog.max_rec, 1) * cxs;
+        L.group = S;
+        if (n > 12 && pl.prog.passes.size() == 1 && pl.prog.passes[0].state && rec * S > kGroupRecBytes)
+            L.group = (int)std::min<size_t>(S, std::max<size_t>(kGroupSlots, kGroupRecBytes / rec / kGroupSlots * kGroupSlots));
+        L.areas.rec_stride = align256(rec * L.group);
         const size_t one = L.areas.wt_stride + L.areas.rec_stride, passes = pl.prog.passes.size();
         L.window = (int)std::max<size_t>(1, std::min<size_t>({32, passes, ((size_t)8 << 20) / one}));
         L.wtab = take(L.areas.wt_stride * L.window);
@@ -999,6 +1011,7 @@ static TrajLayout prep_layout(const TrajPrep &prep, int T)
     pl.fused = prep.fused;
     // only the table sizes of the program enter the layout
     pl.prog.passes.resize(prep.prog.passes.size());
+    if (!pl.prog.passes.empty()) pl.prog.passes[0].state = prep.prog.passes[0].state;
     pl.prog.stages.resize(prep.prog.stages.size());
     pl.prog.rounds.resize(prep.prog.rounds.size());
     pl.prog.ops.resize(prep.prog.ops.size());
@@ -1104,9 +1117,24 @@ static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char
             char *rec = B + L.rec + at * L.areas.rec_stride;
             uint64_t *otab = (uint64_t *)(B + L.wtab + at * L.areas.wt_stride);
             char *wtab = (char *)otab + L.areas.otab_bytes;
+            if (P.passes[p].state) {
+                // one workgroup per slot holds the state, the slots of a record group in one launch; the
+                // overlaps from the stored states
+                for (int s0 = 0; s0 < S; s0 += L.group) {
+                    const int slots = std::min(L.group, S - s0);
+                    QS_HIP(launch_pass_prep(dt, S, s0, slots, &P.passes[p], 1, (int)p, pdv, tab, gdev, rec, L.areas,
+                                            (int64_t)init_index, dyn, st));
+                    QS_HIP(launch_state_pass((char *)psi + (amp_bytes(dt) << n) * (size_t)s0, dt, n, slots, &P.passes[p],
+                                             (int)p, init, pdv, rec, st, dyn));
+                }
+                if (overlaps)
+                    QS_HIP(launch_overlaps(psi, 0, psi, dt, n, S, pmarked, (double *)(B + L.partials),
+                                           (double *)(B + L.out), st, dyn));
+                return QS_OK;
+            }
             if (at == 0) {
                 const int count = (int)std::min<size_t>(L.window, P.passes.size() - p);
-                QS_HIP(launch_pass_prep(dt, S, &P.passes[p], count, (int)p, pdv, tab, gdev, rec, L.areas,
+                QS_HIP(launch_pass_prep(dt, S, 0, S, &P.passes[p], count, (int)p, pdv, tab, gdev, rec, L.areas,
                                         (int64_t)init_index, dyn, st));
                 for (int k = 0; k < count; ++k) {
                     const PassDesc &pk = P.passes[p + k];
@@ -1118,18 +1146,8 @@ static qs_status enqueue_compute(const TrajPrep &prep, const TrajLayout &L, char
                         blocks = blocks || P.rounds[ri].block_rec >= 0;
                     if (blocks) QS_HIP(launch_block_prep(dt, S, &pk, pdv, rk, st));
                 }
-                if (!P.passes[p].state)
-                    QS_HIP(launch_pass_jobs(dt, S, &P.passes[p], count, (int)p, pdv, rec, otab, L.areas, init,
-                                            (int64_t)init_index, dyn, st));
-            }
-            if (P.passes[p].state) {
-                // one workgroup per slot holds the state: every slot in one launch, the overlaps
-                // from the stored states
-                QS_HIP(launch_state_pass(psi, dt, n, S, &P.passes[p], (int)p, init, pdv, rec, st, dyn));
-                if (overlaps)
-                    QS_HIP(launch_overlaps(psi, 0, psi, dt, n, S, pmarked, (double *)(B + L.partials),
-                                           (double *)(B + L.out), st, dyn));
-                return QS_OK;
+                QS_HIP(launch_pass_jobs(dt, S, &P.passes[p], count, (int)p, pdv, rec, otab, L.areas, init,
+                                        (int64_t)init_index, dyn, st));
             }
             if (p + 1 < P.passes.size() || !overlaps) {
                 QS_HIP(launch_fused_pass(psi, dt, n, S, &P.passes[p], (int)p, init, (int64_t)init_index, pdv,

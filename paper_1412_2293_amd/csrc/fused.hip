@@ -226,27 +226,28 @@ __global__ void k_pass_jobs(int S, int pass0, int fill_first, uint64_t basis, co
 constexpr double kShearMin = 0x1p-60;
 
 // One thread per (slot, op), then one wave per (slot, stage) for the products of the stages' factors
-// alpha.  blockIdx.y: the pass, pass0 + blockIdx.y of the program, with its own record area; a launch
-// per pass took 5 us of a chain of loads for 0.2 ms passes (Grover n = 20), the same as one for 32.
+// alpha, for the slots slot_base, ..., slot_base + slots - 1 of S.  blockIdx.y: the pass, pass0 + blockIdx.y
+// of the program, with its own record area; a launch per pass took 5 us of a chain of loads for 0.2 ms
+// passes (Grover n = 20), the same as one for 32.
 // Few threads, each with a chain of loads and products: the descriptors are read together, and no bound on
 // the workgroup is given, with which the compiler moves the factors from scratch memory to the LDS (QFT
 // n = 8, complex<float>, 3001 slots: 24.6 us with a bound of 128 threads, 16.0 without).
 template <typename R>
-__global__ void k_pass_prep(int S, int pass0, ProgramDev prog, const double *tab, const qs_gate *gates, char *rec_base,
-                            uint64_t basis, const RunParams *dyn, PassAreas ar)
+__global__ void k_pass_prep(int S, int slot_base, int slots, int pass0, ProgramDev prog, const double *tab,
+                            const qs_gate *gates, char *rec_base, uint64_t basis, const RunParams *dyn, PassAreas ar)
 {
     const PassDesc *pd = prog.passes + pass0 + blockIdx.y;
     const int expand = pd->expand, op_begin = pd->op_begin, n_ops = pd->op_end - op_begin, rec_size = pd->rec_size;
     const int threads_log = pd->K - pd->RB;
     const int stage_begin = pd->stage_begin, n_stages = pd->stage_end - stage_begin;
-    const int op_blocks = (int)(((int64_t)n_ops * S + 127) / 128);
+    const int op_blocks = (int)(((int64_t)n_ops * slots + 127) / 128);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const OpDesc op = prog.ops[i < (int64_t)n_ops * S ? op_begin + (int)(i % n_ops) : 0];
+    const OpDesc op = prog.ops[i < (int64_t)n_ops * slots ? op_begin + (int)(i % n_ops) : 0];
     if (expand) return;   // (launch_expand_prep)
     cxf<R> *rec_all = reinterpret_cast<cxf<R> *>(rec_base + blockIdx.y * ar.rec_stride);
     if ((int)blockIdx.x >= op_blocks) {
         const int64_t w = (int64_t)((int)blockIdx.x - op_blocks) * 2 + (threadIdx.x >> 6);
-        if (w >= (int64_t)S * n_stages) return;
+        if (w >= (int64_t)slots * n_stages) return;
         const int slot = (int)(w / n_stages), lane = (int)(threadIdx.x & 63u);
         const StageDesc sd = prog.stages[stage_begin + (int)(w % n_stages)];
         if (sd.scale_rec < 0) return;
@@ -254,7 +255,7 @@ __global__ void k_pass_prep(int S, int pass0, ProgramDev prog, const double *tab
         for (int oi = sd.op_begin + lane; oi < sd.op_end; oi += 64) {
             const OpDesc &op = prog.ops[oi];
             if (!(op.flags & OPF_SHEAR)) continue;
-            f *= tab[((uint64_t)op.gate * S + slot) * 8];
+            f *= tab[((uint64_t)op.gate * S + slot_base + slot) * 8];
         }
         for (int off = 32; off > 0; off >>= 1) f *= __shfl_xor(f, off, 64);
         // too small a product (or NaN): the stage runs the matrices themselves, the entry is (1, 0)
@@ -263,18 +264,18 @@ __global__ void k_pass_prep(int S, int pass0, ProgramDev prog, const double *tab
             rec_all[(size_t)slot * rec_size + sd.scale_rec] = sheared ? cxf<R>{(R)f, (R)1} : cxf<R>{(R)1, (R)0};
         return;
     }
-    if (i >= (int64_t)n_ops * S) return;
+    if (i >= (int64_t)n_ops * slots) return;
     if (dyn) basis = dyn->init;
     const int slot = (int)(i / n_ops);
     cxf<R> *blk = rec_all + (size_t)slot * rec_size;
     cxf<R> *rec = blk + op.rec;
     auto tabc = [&](int g) {
-        const double *t = tab + ((uint64_t)g * S + slot) * 8;
+        const double *t = tab + ((uint64_t)g * S + slot_base + slot) * 8;
         return make_double2(t[0], t[1]);
     };
     auto put = [&](cxf<R> *dst, double2 v) { *dst = cxf<R>{(R)v.x, (R)v.y}; };
     if (op.type == OP_U1) {
-        const double *t = tab + ((uint64_t)op.gate * S + slot) * 8;
+        const double *t = tab + ((uint64_t)op.gate * S + slot_base + slot) * 8;
         const bool chain = (op.flags & OPF_CHAIN) != 0;
         double2 uni = make_double2(1.0, 0.0);
         if (op.flags & OPF_SHEAR) {
@@ -348,26 +349,26 @@ size_t fused_lds_bytes(qs_dtype dt, int K)
     return (size_t(1) << K) * (dt == QS_C64 ? 8 : 16);
 }
 
-hipError_t launch_pass_prep(qs_dtype dt, int S, const PassDesc *h, int count, int pass0, ProgramDev prog,
-                            const double *tab, const qs_gate *gates_dev, void *rec, const PassAreas &ar, int64_t basis,
-                            const RunParams *dyn, hipStream_t st)
+hipError_t launch_pass_prep(qs_dtype dt, int S, int slot_base, int slots, const PassDesc *h, int count, int pass0,
+                            ProgramDev prog, const double *tab, const qs_gate *gates_dev, void *rec, const PassAreas &ar,
+                            int64_t basis, const RunParams *dyn, hipStream_t st)
 {
     uint64_t blocks = 0, entries = 0;
     for (int p = 0; p < count; ++p) {
-        const uint64_t tot = (uint64_t)(h[p].op_end - h[p].op_begin) * S;
+        const uint64_t tot = (uint64_t)(h[p].op_end - h[p].op_begin) * slots;
         if (tot == 0 || h[p].expand) continue;
-        blocks = std::max(blocks, (tot + 127) / 128 + ((uint64_t)S * (h[p].stage_end - h[p].stage_begin) + 1) / 2);
+        blocks = std::max(blocks, (tot + 127) / 128 + ((uint64_t)slots * (h[p].stage_end - h[p].stage_begin) + 1) / 2);
         entries += (uint64_t)h[p].rec_size;
     }
     if (blocks == 0) return hipSuccess;
-    TimedLaunch tl("prep", (double)S * entries * (dt == QS_C64 ? 8 : 16), st);
+    TimedLaunch tl("prep", (double)slots * entries * (dt == QS_C64 ? 8 : 16), st);
     const dim3 grid((unsigned)blocks, (unsigned)count);
     if (dt == QS_C64)
-        hipLaunchKernelGGL(k_pass_prep<float>, grid, dim3(128), 0, st, S, pass0, prog, tab, gates_dev, (char *)rec,
-                           (uint64_t)basis, dyn, ar);
+        hipLaunchKernelGGL(k_pass_prep<float>, grid, dim3(128), 0, st, S, slot_base, slots, pass0, prog, tab, gates_dev,
+                           (char *)rec, (uint64_t)basis, dyn, ar);
     else
-        hipLaunchKernelGGL(k_pass_prep<double>, grid, dim3(128), 0, st, S, pass0, prog, tab, gates_dev, (char *)rec,
-                           (uint64_t)basis, dyn, ar);
+        hipLaunchKernelGGL(k_pass_prep<double>, grid, dim3(128), 0, st, S, slot_base, slots, pass0, prog, tab, gates_dev,
+                           (char *)rec, (uint64_t)basis, dyn, ar);
     return hipGetLastError();
 }
 

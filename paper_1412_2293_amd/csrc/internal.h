@@ -333,11 +333,11 @@ struct PassAreas {
     uint64_t rec_stride, wt_stride, otab_bytes;
 };
 
-// Records of the passes pass0, ..., pass0 + count - 1 (pass_host: the first one's descriptor) for all S
-// slots, except those marked `expand`.
-hipError_t launch_pass_prep(qs_dtype dt, int S, const PassDesc *pass_host, int count, int pass0, ProgramDev prog,
-                            const double *tab, const qs_gate *gates_dev, void *rec, const PassAreas &ar, int64_t basis,
-                            const RunParams *dyn, hipStream_t st);
+// Records of the passes pass0, ..., pass0 + count - 1 (pass_host: the first one's descriptor), except those
+// marked `expand`, for the slots slot_base, ..., slot_base + slots - 1 of S (rec: slot_base's come first).
+hipError_t launch_pass_prep(qs_dtype dt, int S, int slot_base, int slots, const PassDesc *pass_host, int count,
+                            int pass0, ProgramDev prog, const double *tab, const qs_gate *gates_dev, void *rec,
+                            const PassAreas &ar, int64_t basis, const RunParams *dyn, hipStream_t st);
 // Sets the fused kernels' LDS limit (done by the first launch otherwise); call before capturing
 // a graph.
 hipError_t fused_prepare_attributes();
@@ -365,7 +365,7 @@ hipError_t launch_expand_pass(void *psi, qs_dtype dt, int n, int S, const PassDe
                               const uint64_t *otab, hipStream_t st, const RunParams *dyn, double *ovl, int slot_base,
                               int slots);
 // The whole program of a state that fits one tile (PassDesc::state), one workgroup per slot, from
-// the basis state |init>.  state_shape: whether 2^n amplitudes with 2^RB per thread run so;
+// the basis state |init>, for S slots whose states start at psi and whose records at rec.  state_shape: whether 2^n amplitudes with 2^RB per thread run so;
 // state_reg_bits: the register bits of the automatic plan (0: the state does not fit).
 hipError_t launch_state_pass(void *psi, qs_dtype dt, int n, int S, const PassDesc *pass_host, int pass_index,
                              int64_t init, ProgramDev prog, const void *rec, hipStream_t st, const RunParams *dyn);
