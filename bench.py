@@ -34,9 +34,14 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
+# The files that the kernels of the stored profile are compiled from, and the planner that lays their program.
+PROFILED_SOURCES = ("fused.hip", "fused_c64.hip", "fused_kernel.h", "expand.hip", "regops.h", "cplx.h", "internal.h",
+                    "planner.cpp")
+
+
 def source_hash():
     h = hashlib.sha256()
-    for f in ("fused.hip", "fused_kernel.h", "expand.hip", "planner.cpp"):
+    for f in PROFILED_SOURCES:
         with open(os.path.join(ROOT, "paper_1412_2293_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
