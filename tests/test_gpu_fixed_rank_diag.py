@@ -79,3 +79,31 @@ def test_diagonal_step_equals_the_general_form(n):
     a, b = out[0][2], out[1][2]
     G = (a.conj() @ b.T).cpu().numpy()     # equal up to a phase per column
     assert np.allclose(np.sum(np.abs(G) ** 2), np.sum(np.abs((a.conj() @ a.T).cpu().numpy()) ** 2), atol=1e-11)
+
+
+@pytest.mark.parametrize("n", [16, 19])
+def test_diagonal_steps_give_the_general_density_matrix(n):
+    """||rho_a - rho_b||_F of the compact and the general form, so that components outside the other's columns
+    count too: with the columns side by side, M = (A, B) = Q R, it is the norm of R diag(1, -1) R^dagger.  Both
+    round each of five steps to about 1e-15 of their Gram matrices and truncate to the same rank, an error that
+    grows by the inverse gap of the spectrum there; 1e-10 leaves a factor of 10^4 for it."""
+    rng = np.random.default_rng(100 + n)
+    ops = _diagonal_set(rng, 3)
+    near = ops.copy()
+    near[0, 0, 1] = 1e-300
+    cols, ranks = [], []
+    for o in (ops, near):
+        g = np.random.default_rng(4)
+        fr = q.FixedRank(n, 8, q.C128)
+        fr.init_basis(1)
+        for k, (a, b) in enumerate([(0, n - 1), (n - 2, 1), (3, 2), (n - 4, 8), (6, n - 1)]):
+            for qb in (a, b):
+                fr.apply_gate(Gate(U1, q0=qb, m=_haar(g, 2)))
+            ranks.append(fr.apply_kraus2(a, b, o))
+        rank, lt = fr.info()
+        cols.append(fr.columns()[:rank].cpu().numpy().T * math.exp(0.5 * lt))
+    assert ranks[:5] == ranks[5:] and max(ranks) == 8
+    r = cols[0].shape[1]
+    R = np.linalg.qr(np.hstack(cols), mode="r")
+    dist = np.linalg.norm(R @ np.diag([1.0] * r + [-1.0] * r) @ R.conj().T)
+    assert dist <= 1e-10, dist
