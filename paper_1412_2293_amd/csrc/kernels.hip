@@ -687,25 +687,24 @@ __global__ void k_scale_pattern(R *psi, int n, uint64_t mask, uint64_t value, in
 }
 
 // A controlled phase or a CNOT on both sides of vec(rho) in one sweep, over the index bits b[0], b[1]
-// (columns) and b[2], b[3] (rows).  A thread takes one of the six parts of a group of 16 entries
-// (uniform over the block but for small matrices), so only what changes is touched:
+// (columns) and b[2], b[3] (rows).  A thread takes what changes of a group of 16 entries:
 //   CP: the six entries with exactly one of row and column selected, times f or conj(f) (with both
 //       selected the phases cancel: f conj(f) over the averaged phase's exp(-e^2) is 1);
 //   CNOT: the six pairs that swap (control b[0] / b[2]).
-// Three sweeps of the averaged phase over quarters, with the index built bit by bit, took 29 us per
-// gate (11 qubits, complex<double>) and this takes 11; two sweeps of a CNOT 26 and 19.
+// All of a group in one thread, so that the entries that share a line with it are read once (11 qubits,
+// complex<double>, us, controlled phase and CNOT on qubits 0 and 1: three and two sweeps 49 and 47, six threads
+// per group 27 and 47, one 25 and 31; 13 qubits, complex<double>: 605 and 644, 556 and 1040, 423 and 412).
 struct Bits4 {
     int b[4];        // the four index bits, local bit k -> index bit b[k]
     int sorted[4];   // the same, ascending (for inserting the zero bits)
 };
 
 template <typename R, bool CNOT>
-__global__ void __launch_bounds__(256) k_dm_pair(R *psi, Bits4 bits, int log_groups, uint64_t total, double fre, double fim)
+__global__ void __launch_bounds__(256) k_dm_pair(R *psi, Bits4 bits, uint64_t total, double fre, double fim)
 {
     for (uint64_t it = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; it < total;
          it += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t part = (uint32_t)(it >> log_groups);
-        uint64_t base = it & ((1ull << log_groups) - 1ull);
+        uint64_t base = it;
 #pragma unroll
         for (int k = 0; k < 4; ++k) base = ins0(base, bits.sorted[k]);
         auto at = [&](uint32_t l) {
@@ -715,24 +714,24 @@ __global__ void __launch_bounds__(256) k_dm_pair(R *psi, Bits4 bits, int log_gro
                 if ((l >> k) & 1u) i |= 1ull << bits.b[k];
             return i;
         };
-        const uint32_t o = part % 3u;
-        if constexpr (CNOT) {
-            // side 0, 1: the other side's control is 0 and its target (part / 3) keeps its value;
-            // o = 2: both controls are 1 and both targets flip, column target 0 or 1
-            const uint32_t t = part / 3u;
-            const uint32_t a = o == 0 ? 0x1u | t << 3 : o == 1 ? 0x4u | t << 1 : 0x5u | t << 1;
-            const uint32_t flip = o == 0 ? 0x2u : o == 1 ? 0x8u : 0xAu;
-            const uint64_t i = at(a), k = at(a ^ flip);
-            const cx<R> x = sload(psi, i), y = sload(psi, k);
-            sstore(psi, i, y);
-            sstore(psi, k, x);
-        } else {
-            const bool row = part >= 3u;
-            const uint32_t l = row ? 0xCu | o : 0x3u | o << 2;
-            const uint64_t i = at(l);
-            const cx<R> x = sload(psi, i);
-            const R cr = (R)fre, ci = row ? (R)fim : -(R)fim;
-            sstore(psi, i, cx<R>{cr * x.re - ci * x.im, cr * x.im + ci * x.re});
+        // local indices of the six: CNOT pairs (first, first ^ flip), CP entries (columns, then rows)
+        constexpr uint32_t first[6] = {0x1u, 0x4u, 0x5u, 0x9u, 0x6u, 0x7u}, flip[3] = {0x2u, 0x8u, 0xAu};
+        constexpr uint32_t sel[6] = {0x3u, 0x7u, 0xBu, 0xCu, 0xDu, 0xEu};
+        cx<R> x[6], y[6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            x[k] = sload(psi, at(CNOT ? first[k] : sel[k]));
+            if constexpr (CNOT) y[k] = sload(psi, at(first[k] ^ flip[k % 3]));
+        }
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            if constexpr (CNOT) {
+                sstore(psi, at(first[k]), y[k]);
+                sstore(psi, at(first[k] ^ flip[k % 3]), x[k]);
+            } else {
+                const R cr = (R)fre, ci = k >= 3 ? (R)fim : -(R)fim;
+                sstore(psi, at(sel[k]), cx<R>{cr * x[k].re - ci * x[k].im, cr * x[k].im + ci * x[k].re});
+            }
         }
     }
 }
@@ -1252,16 +1251,15 @@ static hipError_t launch_dm_pair(void *psi, qs_dtype dt, int n, int q0, int q1, 
                                  hipStream_t st)
 {
     Bits4 b{{q0, q1, q0 + n, q1 + n}, {std::min(q0, q1), std::max(q0, q1), std::min(q0, q1) + n, std::max(q0, q1) + n}};
-    const int log_groups = 2 * n - 4;
-    const uint64_t total = 6ull << log_groups;
-    TimedLaunch tl("dm_pair", (cnot ? 4.0 : 2.0) * (double)total * amp_bytes(dt), st);
+    const uint64_t total = 1ull << (2 * n - 4);
+    TimedLaunch tl("dm_pair", (cnot ? 24.0 : 12.0) * (double)total * amp_bytes(dt), st);
     const dim3 grid(blocks_for(total, 256)), block(256);
     if (dt == QS_C64) {
-        if (cnot) hipLaunchKernelGGL((k_dm_pair<float, true>), grid, block, 0, st, (float *)psi, b, log_groups, total, fre, fim);
-        else hipLaunchKernelGGL((k_dm_pair<float, false>), grid, block, 0, st, (float *)psi, b, log_groups, total, fre, fim);
+        if (cnot) hipLaunchKernelGGL((k_dm_pair<float, true>), grid, block, 0, st, (float *)psi, b, total, fre, fim);
+        else hipLaunchKernelGGL((k_dm_pair<float, false>), grid, block, 0, st, (float *)psi, b, total, fre, fim);
     } else {
-        if (cnot) hipLaunchKernelGGL((k_dm_pair<double, true>), grid, block, 0, st, (double *)psi, b, log_groups, total, fre, fim);
-        else hipLaunchKernelGGL((k_dm_pair<double, false>), grid, block, 0, st, (double *)psi, b, log_groups, total, fre, fim);
+        if (cnot) hipLaunchKernelGGL((k_dm_pair<double, true>), grid, block, 0, st, (double *)psi, b, total, fre, fim);
+        else hipLaunchKernelGGL((k_dm_pair<double, false>), grid, block, 0, st, (double *)psi, b, total, fre, fim);
     }
     return hipGetLastError();
 }
