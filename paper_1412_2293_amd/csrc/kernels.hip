@@ -534,6 +534,9 @@ __global__ void __launch_bounds__(256) k_2q(R *psi, int n, int qa, int qb, const
 
 // Dense two-qubit sweep of complex<float> with qubit 0: both its values lie in one 16-byte vector, so a
 // thread's group is the vectors at the other qubit's two values.  m: local index bit(0) + 2 bit(hi).
+// NT: streaming accesses, for states that the 256 MiB cache does not hold (qubits 0 and 12, us with and
+// without: n = 25 80 and 63, n = 26 161 and 177).
+template <bool NT>
 __global__ void __launch_bounds__(256) k_2q_low(float *psi, int n, int hi, M32 m32, int log_items, uint64_t total)
 {
   cx<float> m[16];
@@ -544,22 +547,33 @@ __global__ void __launch_bounds__(256) k_2q_low(float *psi, int n, int hi, M32 m
     float *p = psi + ((it >> log_items) << (n + 1));
     const uint64_t i0 = ins0((it & ((1ull << log_items) - 1)) * 2, hi), i1 = i0 | (1ull << hi);
     cx<float> a[4];
-    vload_nt(p, i0, a);
-    vload_nt(p, i1, a + 2);
+    if constexpr (NT) {
+        vload_nt(p, i0, a);
+        vload_nt(p, i1, a + 2);
+    } else {
+        vload(p, i0, a);
+        vload(p, i1, a + 2);
+    }
     cx<float> y[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
         y[r] = cfma(m[4 * r + 3], a[3], cfma(m[4 * r + 2], a[2], cfma(m[4 * r + 1], a[1], cmul(m[4 * r], a[0]))));
-    vstore_nt(p, i0, y);
-    vstore_nt(p, i1, y + 2);
+    if constexpr (NT) {
+        vstore_nt(p, i0, y);
+        vstore_nt(p, i1, y + 2);
+    } else {
+        vstore(p, i0, y);
+        vstore(p, i1, y + 2);
+    }
   }
 }
 
 // The same with the other qubit among the lane bits (hi <= 6): every lane loads its own vector, so that
 // a wave's access is one contiguous 1 KiB, and takes the other one from lane l ^ 2^(hi - 1).  Bound by HBM:
 // n = 27, qubits 0 and 1: 417 us with four loads of 8 bytes per thread, 380 with two of 16 to a group's
-// own thread, 347 here.  Vectors per slot are a multiple of 256 U.
-template <int U>
+// own thread, 347 here; n = 25 93, and 62 without streaming accesses (84 with).  Vectors per slot are a
+// multiple of 256 U.
+template <int U, bool NT>
 __global__ void __launch_bounds__(256) k_2q_low_lane(float *psi, int n, int hi, M32 m32, int log_items, uint64_t total)
 {
   const int lmask = 1 << (hi - 1);
@@ -581,7 +595,8 @@ __global__ void __launch_bounds__(256) k_2q_low_lane(float *psi, int n, int hi, 
     for (int u = 0; u < U; ++u) {
         const uint64_t it = blk * (256 * U) + (uint64_t)u * 256 + threadIdx.x;
         at[u] = psi + ((it >> log_items) << (n + 1)) + 4 * (it & ((1ull << log_items) - 1));
-        vload_nt(at[u], 0, a[u]);
+        if constexpr (NT) vload_nt(at[u], 0, a[u]);
+        else vload(at[u], 0, a[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -590,7 +605,8 @@ __global__ void __launch_bounds__(256) k_2q_low_lane(float *psi, int n, int hi, 
         for (int k = 0; k < 2; ++k) o[k] = {__shfl_xor(a[u][k].re, lmask), __shfl_xor(a[u][k].im, lmask)};
         y[0] = cfma(k0[3], o[1], cfma(k0[2], o[0], cfma(k0[1], a[u][1], cmul(k0[0], a[u][0]))));
         y[1] = cfma(k1[3], o[1], cfma(k1[2], o[0], cfma(k1[1], a[u][1], cmul(k1[0], a[u][0]))));
-        vstore_nt(at[u], 0, y);
+        if constexpr (NT) vstore_nt(at[u], 0, y);
+        else vstore(at[u], 0, y);
     }
   }
 }
@@ -1340,13 +1356,18 @@ hipError_t launch_sweep_2q(void *psi, qs_dtype dt, int n, int S, int qa, int qb,
                 for (int k = 0; k < 2; ++k) m.v[2 * (4 * sw(r) + sw(c)) + k] = m32[2 * (4 * r + c) + k];
         const int hi = std::max(qa, qb);
         const uint64_t vectors = (uint64_t)S << (n - 1);
+        const bool nt = vectors * 16 > (256ull << 20);
+#define QS_2Q_LOW(KERNEL, ITEMS, PER, LOG)                                                                              \
+    hipLaunchKernelGGL(KERNEL, dim3(blocks_for(ITEMS, PER)), dim3(256), 0, st, (float *)psi, n, hi, m, LOG, ITEMS)
         // (the lane form needs whole workgroups of 512 vectors in a slot)
-        if (hi <= 6 && n - 1 >= 9)
-            hipLaunchKernelGGL(k_2q_low_lane<2>, dim3(blocks_for(vectors, 512)), dim3(256), 0, st, (float *)psi, n, hi, m,
-                               n - 1, vectors);
-        else
-            hipLaunchKernelGGL(k_2q_low, dim3(blocks_for(vectors / 2, 256)), dim3(256), 0, st, (float *)psi, n, hi, m,
-                               n - 2, vectors / 2);
+        if (hi <= 6 && n - 1 >= 9) {
+            if (nt) QS_2Q_LOW((k_2q_low_lane<2, true>), vectors, 512, n - 1);
+            else QS_2Q_LOW((k_2q_low_lane<2, false>), vectors, 512, n - 1);
+        } else {
+            if (nt) QS_2Q_LOW(k_2q_low<true>, vectors / 2, 256, n - 2);
+            else QS_2Q_LOW(k_2q_low<false>, vectors / 2, 256, n - 2);
+        }
+#undef QS_2Q_LOW
         return hipGetLastError();
     }
     if (dt == QS_C64 ? sweep_2q_lane((float *)psi, n, S, qa, qb, m32, st)
