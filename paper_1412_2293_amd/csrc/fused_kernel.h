@@ -382,22 +382,27 @@ __global__ void __launch_bounds__((kWideTile<R, RB>) ? 256 : 512)
     // two register bits only multiplies its factor into the thread's product for those bits, and the
     // products reach the registers before the next dense op or exchange.  Applied one by one, each op
     // passed over half or a quarter of the registers, with a test per register (density matrix of the
-    // 12-qubit QFT, complex<float>, 198 such ops in three passes: 284 us in the passes, 182 with the
-    // products).
+    // 12-qubit QFT, 198 such ops in three passes: complex<float>, 282 us in the passes one by one, 195 with
+    // the products; complex<double>, 330 and 287).  The products are held at twice the precision: in the
+    // type's own they took 189 and 250 us, but equal layers of such ops came out up to four times
+    // further off than one by one.
     constexpr bool DEFER = ZV == 7;
-    cxf<R> dw1[RB], dw2 = {(R)1, (R)0};
+    cxprod<R> dw1[RB], dw2;
+    dw2.clear();
 #pragma unroll
     for (int k = 0; k < RB; ++k) dw1[k] = dw2;
     uint32_t dirty = 0;          // bit k: dw1[k] holds factors; bit 8: dw2, for the register bits in dpair
     uint32_t dpair = 0;
     auto flush = [&]() {
         if (dirty == 0) return;
-        const cxf<R> one = {(R)1, (R)0};
         auto single = [&](auto pc) {
             constexpr int P = decltype(pc)::value;
             if (P < RB && ((dirty >> P) & 1u)) {
-                phase_on_bit<R, RB, P % RB>(a, dw1[P % RB]);
-                dw1[P % RB] = one;
+                const cxf<R> hi = dw1[P % RB].hi(), lo = dw1[P % RB].lo();
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if ((r >> P) & 1) a[r] = mul2(hi, lo, a[r]);
+                dw1[P % RB].clear();
             }
         };
         single(std::integral_constant<int, 0>{});
@@ -405,10 +410,11 @@ __global__ void __launch_bounds__((kWideTile<R, RB>) ? 256 : 512)
         single(std::integral_constant<int, 2>{});
         single(std::integral_constant<int, 3>{});
         if (dirty & 256u) {
+            const cxf<R> hi = dw2.hi(), lo = dw2.lo();
 #pragma unroll
             for (int r = 0; r < NR; ++r)
-                if (((uint32_t)r & dpair) == dpair) a[r] = tvec(mul(dw2, cx<R>(a[r])));
-            dw2 = one;
+                if (((uint32_t)r & dpair) == dpair) a[r] = mul2(hi, lo, a[r]);
+            dw2.clear();
         }
         dirty = 0;
     };
@@ -419,14 +425,14 @@ __global__ void __launch_bounds__((kWideTile<R, RB>) ? 256 : 512)
             if ((dirty & 256u) && pair != dpair) flush();
             dpair = pair;
             dirty |= 256u;
-            dw2 = mul(dw2, w);
+            dw2.times(w);
             return;
         }
         dirty |= 1u << p0;
-        if (p0 == 0) dw1[0] = mul(dw1[0], w);
-        else if (RB > 1 && p0 == 1) dw1[1 % RB] = mul(dw1[1 % RB], w);
-        else if (RB > 2 && p0 == 2) dw1[2 % RB] = mul(dw1[2 % RB], w);
-        else dw1[RB - 1] = mul(dw1[RB - 1], w);
+        if (p0 == 0) dw1[0].times(w);
+        else if (RB > 1 && p0 == 1) dw1[1 % RB].times(w);
+        else if (RB > 2 && p0 == 2) dw1[2 % RB].times(w);
+        else dw1[RB - 1].times(w);
     };
     // The diagonal ops from oi on, up to the next dense op or the round's end: their descriptors and
     // factors four at a time, so that four ops wait on two scalar loads in turn instead of eight.

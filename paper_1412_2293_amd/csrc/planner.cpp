@@ -924,8 +924,8 @@ qs_status plan_fused(const qs_gate *gates, int n_gates, int n, int K, int RB, in
             if (u1 == 0 && pd.mixed_ops && !pd.blocks) pd.zin_ops = 5;
             // Its diagonal ops' products are collected in tiles of 8 or 16 registers, where there are at
             // least two such ops for each dense op and round, which end a collection (density matrix of
-            // the QFT, 13 qubits: complex<float>, 16 registers, 1161 us one by one, 800 collected;
-            // complex<double>, 8 registers, 1600 and 1265.  Grover's 13 qubits, one diagonal op per layer,
+            // the QFT, 13 qubits: complex<float>, 16 registers, 1110 us one by one, 785 collected;
+            // complex<double>, 8 registers, 1540 and 1375.  Grover's 13 qubits, one diagonal op per layer,
             // complex<double>: 14.4 ms and 14.9).
             if (pd.zin_ops == 5) {
                 int collect = 0, ends = pd.round_end - pd.round_begin;
