@@ -44,7 +44,7 @@ void clear_error();
 // ---------------------------------------------------------------------------------------
 constexpr int kMaxTileBits = 15;
 constexpr int kMaxRegBits = 4;
-constexpr int kPhaseTable = 4 + 32 + 16;   // reg + lo + hi entries of a phase block
+constexpr int kPhaseTable = 4 + 32 + 16;   // reg + lo + hi entries of a phase block, without top
 
 // Entries of a phase block before its outer phases, with 2^threads_log threads per tile.
 __host__ __device__ inline int phase_table(int threads_log) { return kPhaseTable + (threads_log > 9 ? 2 : 0); }
@@ -118,7 +118,7 @@ struct PassDesc {
     int32_t expand;               // zin_ops 3 with enough targets: the pass is the product of its
                                   // targets' factors (see k_expand) and runs as one
     int32_t state;                // the tile is the whole state: the program runs as StateOps (2:
-                                  // every one-qubit op a sheared one without phases, no two-qubit op)
+                                  // every one-qubit op real and without phases, no two-qubit op)
     int16_t xop[16];              // expand: op (relative to op_begin) of tile-local bit j, -1 none
 };
 
@@ -298,7 +298,6 @@ hipError_t launch_overlap_final(const void *psi, qs_dtype dt, int n, int S, int 
 hipError_t launch_overlaps(const void *ref_psi, int ref_slot, const void *psi, qs_dtype dt, int n,
                            int S, int64_t marked, double *partials, double *out, hipStream_t st,
                            const RunParams *dyn = nullptr);
-// <psi|rho|psi> and Tr rho over vec(rho) of n qubits: out = (Re f, Im f, Re tr, Im tr).
 // out[0..4] and out[5..9] as launch_overlaps gives them for (a, b) and (a, a), one slot each, from one
 // pass over both states (out[6] = 0); partials: 6 << red_log_blocks doubles.
 hipError_t launch_fidelity(const void *a, const void *b, qs_dtype dt, int n, double *partials, double *out,
@@ -307,6 +306,7 @@ hipError_t launch_fidelity(const void *a, const void *b, qs_dtype dt, int n, dou
 // has; and the CNOT of both sides.
 hipError_t launch_dm_cp(void *rho, qs_dtype dt, int n, int q0, int q1, double fre, double fim, hipStream_t st);
 hipError_t launch_dm_cnot(void *rho, qs_dtype dt, int n, int control, int target, hipStream_t st);
+// <psi|rho|psi> and Tr rho over vec(rho) of n qubits: out = (Re f, Im f, Re tr, Im tr).
 hipError_t launch_dm_expect(const void *rho, const void *psi, qs_dtype dt, int n,
                             double *partials, double *out, hipStream_t st);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t st);
@@ -365,7 +365,8 @@ hipError_t launch_expand_pass(void *psi, qs_dtype dt, int n, int S, const PassDe
                               const uint64_t *otab, hipStream_t st, const RunParams *dyn, double *ovl, int slot_base,
                               int slots);
 // The whole program of a state that fits one tile (PassDesc::state), one workgroup per slot, from
-// the basis state |init>, for S slots whose states start at psi and whose records at rec.  state_shape: whether 2^n amplitudes with 2^RB per thread run so;
+// the basis state |init>, for S slots whose states start at psi and whose records at rec.
+// state_shape: whether 2^n amplitudes with 2^RB per thread run so;
 // state_reg_bits: the register bits of the automatic plan (0: the state does not fit).
 hipError_t launch_state_pass(void *psi, qs_dtype dt, int n, int S, const PassDesc *pass_host, int pass_index,
                              int64_t init, ProgramDev prog, const void *rec, hipStream_t st, const RunParams *dyn);

@@ -1,15 +1,15 @@
 // Circuits on states that fit one CU's LDS: the whole circuit of a slot in one workgroup.
 //
-// Such a run is a serial chain of gates per slot, with few workgroups on the chip, so its time is
-// the latency of each step and not a rate.  What a gate needs (its descriptor, matrix and phase
-// tables) therefore comes from the LDS, staged once per stage for all its gates by coalesced
-// loads, instead of from two dependent scalar loads per gate that miss the scalar cache (about
-// 1 us per gate on one workgroup); the next gate's descriptor is read while this one runs.
-// Registers hold 2^RB amplitudes per thread, few for small states, so that a slot's gates spread
-// over the CU's four SIMDs; rounds exchange the state through the LDS, in two buffers taken in turn
-// where both fit (one barrier per exchange instead of two).
-// Grover n = 10, 200 trajectories, complex<double>: 512 us as passes, 163 us here; random pairs n = 14, 60 layers,
-// 16 trajectories, complex<float>: 0.98 ms in 15 passes, 0.82 ms here.
+// Such a run is a serial chain of gates per slot.  Up to about 11 qubits its time is the latency of each
+// step and not a rate: what a gate needs (its descriptor, matrix and phase tables) therefore comes from
+// the LDS, staged once per stage for all its gates by coalesced loads, instead of from two dependent
+// scalar loads per gate that miss the scalar cache (about 1 us per gate on one workgroup); the next
+// gate's descriptor is read while this one runs.  At 13 and 14 qubits it is the vector issue of the one
+// CU that holds the slot.  Registers hold 2^RB amplitudes per thread, few for small states, so that a
+// slot's gates spread over the CU's four SIMDs; rounds exchange the state through the LDS, in two
+// buffers taken in turn where that costs no workgroup (one barrier per exchange instead of two).
+// Grover n = 10, complex<double>: 200 trajectories 512 us as passes, 154 us here; one 628 and 155.  Random
+// pairs n = 14, 60 layers, 16 trajectories, complex<float>: 1.01 ms in 18 passes, 0.83 ms here.
 #include <algorithm>
 #include <cmath>
 
